@@ -1,0 +1,748 @@
+"""The work that a user has this library do, as cases that can be timed and
+compared: training steps from a tiny single view to a 40-view keyframe window,
+gradients through autograd, pose gradients of a rig, renders, the dense
+optimiser step, the frequency scheduling, the LoG insertion and the merge.
+
+listed() names the cases, draw() gives more of the same ranges, prepare() makes
+the inputs and the objects that a program keeps, run() is one pass through the
+public entry points, work() the bytes and operations a pass cannot do without,
+and exact() the same results in 64 bits from plain torch.
+"""
+from __future__ import annotations
+
+import collections
+import math
+
+import numpy as np
+import torch
+
+DEVICE = "cuda" if torch.cuda.is_available() else "cpu"
+NEVER = 0xFFFFFFFF  # long-list split that no tile reaches
+SH0 = 0.28209479177387814
+LR = (1.6e-4, 5e-3, 1e-3, 5e-2, 2.5e-3, 2.5e-3 / 20.0)  # the optimiser's defaults
+NAMES = ("mean", "log_scale", "quat", "opacity_logit", "sh")
+
+Cam = collections.namedtuple("Cam", "R t fx fy cx cy width height")
+
+
+# ---------------------------------------------------------------- the cases
+
+def listed():
+    return [
+        # the first iterations on a thumbnail with few Gaussians: latency and launch count
+        dict(name="train_tiny", kind="train", scene="near", views=1, res="64x48", n=2000, degree=0, tile=16, split=1024),
+        # a viewer's frame from a serving loop that may not allocate
+        dict(name="serve_540p", kind="serve", scene="box", views=1, res="960x540", n=60_000, degree=1, tile=16, split=1024),
+        # one full-HD frame of a reconstructed scene
+        dict(name="render_1080p", kind="render", scene="box", views=1, res="1920x1080", n=500_000, degree=3, tile=16, split=1024),
+        # gradients through autograd for a loss of the user's own, cameras of three odd sizes, 8 px tiles
+        dict(name="grads_ragged", kind="grads", scene="street", views=3, res="801x533,1023x577,640x479", n=150_000, degree=2, tile=8, split=1024),
+        # the training step on one frame of a six-camera rig
+        dict(name="train_rig6", kind="train", scene="street", views=6, res="1600x900", n=1_000_000, degree=3, tile=16, split=512),
+        # joint refinement of scene and rig poses at half resolution
+        dict(name="pose_rig6", kind="pose", scene="street", views=6, res="800x450", n=300_000, degree=1, tile=16, split=1024),
+        # the training step on a window of keyframes of uneven resolution
+        dict(name="train_window40", kind="train", scene="street", views=40, res="960x540,1280x720,1920x1080", n=2_000_000, degree=3, tile=16, split=NEVER),
+        # the optimiser on gradients gathered over several backward calls
+        dict(name="adam_1m", kind="adam", n=1_000_000, degree=3),
+        # frequency significance of a rig frame's renders and the frame draw
+        dict(name="freq_rig6", kind="freq", views=6, res="1600x900", factor=1),
+        # the same for frames of mixed size with their levels of detail made first
+        dict(name="freq_levels", kind="freq", views=4, res="960x540,1280x720,1920x1080,750x420", factor=2),
+        # new Gaussians where the renders of a rig frame lack detail
+        dict(name="insert_rig6", kind="insert", views=6, res="1600x900"),
+        # the scene's Gaussians against the samples of one new camera
+        dict(name="merge_1m", kind="merge", views=6, res="1600x900", n=1_000_000),
+    ]
+
+
+def draw(rng):
+    def log_int(lo, hi):
+        return int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+
+    def odd_res(lo, hi, count=1):
+        got = []
+        for _ in range(count):
+            w = log_int(lo, hi)
+            got.append("%dx%d" % (w, max(24, int(w * rng.choice([0.5625, 0.6, 0.667, 0.75])) + rng.randint(-3, 3))))
+        return ",".join(got)
+
+    def smooth_res(count):  # transform lengths with prime factors up to 7, even after halving
+        sides = [(160, 120), (320, 180), (420, 252), (500, 300), (640, 480), (800, 450), (960, 540), (1050, 700), (1280, 720),
+                 (1344, 756), (1600, 900), (1920, 1080)]
+        return ",".join("%dx%d" % rng.choice(sides) for _ in range(count))
+
+    kind = rng.choice(["train", "train", "train", "grads", "pose", "render", "serve", "adam", "freq", "insert", "merge"])
+    tile, split = rng.choice([(8, 1024), (16, 1024), (16, 512), (16, NEVER), (16, 256), (32, 1024)])
+    if kind in ("train", "grads", "pose"):
+        return dict(kind=kind, scene="street", views=rng.randint(1, 12), res=odd_res(160, 1920, rng.randint(1, 3)), n=log_int(3000, 1_000_000),
+                    degree=rng.randint(0, 3), tile=tile, split=split)
+    if kind == "render":
+        return dict(kind=kind, scene=rng.choice(["box", "street"]), views=rng.randint(1, 4), res=odd_res(100, 1920), n=log_int(3000, 1_000_000),
+                    degree=rng.randint(0, 3), tile=tile, split=split)
+    if kind == "serve":
+        return dict(kind=kind, scene="box", views=1, res=odd_res(100, 1280), n=log_int(2000, 80_000), degree=rng.randint(0, 3), tile=tile, split=split)
+    if kind == "adam":
+        return dict(kind=kind, n=log_int(2000, 3_000_000), degree=rng.randint(0, 3))
+    if kind == "freq":
+        return dict(kind=kind, views=rng.randint(1, 16), res=smooth_res(rng.randint(1, 4)), factor=rng.choice([1, 2]))
+    if kind == "insert":
+        return dict(kind=kind, views=rng.randint(1, 8), res=odd_res(160, 1920, rng.randint(1, 2)))
+    return dict(kind=kind, views=rng.randint(1, 8), res=odd_res(160, 1920), n=log_int(3000, 3_000_000))
+
+
+# ------------------------------------------------- inputs, from the seed alone
+
+def _sizes(case):
+    res = [tuple(int(x) for x in r.split("x")) for r in case["res"].split(",")]
+    return [res[v % len(res)] for v in range(case["views"])]
+
+
+def _gen(seed):
+    return torch.Generator(device=DEVICE).manual_seed(int(seed) * 7919 + 11)
+
+
+def _uniform(g, lo, hi, *shape):
+    return torch.rand(*shape, generator=g, device=DEVICE) * (hi - lo) + lo
+
+
+def _normal(g, mu, sd, *shape):
+    return torch.randn(*shape, generator=g, device=DEVICE) * sd + mu
+
+
+def _rig_layout(views):
+    per = 6 if views % 6 == 0 else (5 if views % 5 == 0 else min(views, 4))
+    return per, [v // per for v in range(views)], [v % per for v in range(views)]
+
+
+def _cameras(case, seed):
+    """Street: rings of cameras (a rig) 4 m apart along the road, slightly turned; else one camera at the origin looking along z."""
+    rng = np.random.default_rng(seed)
+    scene = case.get("scene", "street")
+    per, frame, cam = _rig_layout(case["views"])
+    frames = frame[-1] + 1
+    out = []
+    for v, (w, h) in enumerate(_sizes(case)):
+        f = {"near": 60.0 / 64.0, "box": 1400.0 / 1920.0, "street": 0.75}[scene] * w
+        yaw, pitch, roll = np.radians(rng.uniform(-2.0, 2.0, 3)) if scene == "street" else np.zeros(3)
+        c = np.zeros(3)
+        if scene == "street":
+            a = 2 * math.pi * cam[v] / per
+            c = np.array([0.1 * math.sin(a), 0.0, 0.1 * math.cos(a) + 4.0 * (frame[v] - (frames - 1) / 2)])
+            yaw += a
+        cy, sy, cp, sp, cr, sr = math.cos(yaw), math.sin(yaw), math.cos(pitch), math.sin(pitch), math.cos(roll), math.sin(roll)
+        to_world = (np.array([[cy, 0, sy], [0, 1, 0], [-sy, 0, cy]]) @ np.array([[1, 0, 0], [0, cp, -sp], [0, sp, cp]])
+                    @ np.array([[cr, -sr, 0], [sr, cr, 0], [0, 0, 1]]))
+        r = to_world.T.astype(np.float32)
+        out.append(Cam(r, (-(to_world.T @ c)).astype(np.float32), float(np.float32(f)), float(np.float32(f)), w / 2, h / 2, w, h))
+    return out
+
+
+def _gaussians(case, seed):
+    """A scene of n Gaussians: a street corridor (ground and two facades), a box in front of the camera, or a small cloud near it."""
+    g, n, scene = _gen(seed), case["n"], case.get("scene", "street")
+    if scene == "street":
+        ground = torch.rand(n, generator=g, device=DEVICE) < 0.4
+        side = torch.where(torch.rand(n, generator=g, device=DEVICE) < 0.5, -10.0, 10.0)
+        x = torch.where(ground, _uniform(g, -10, 10, n), side + _normal(g, 0, 0.05, n))
+        y = torch.where(ground, _normal(g, 1.6, 0.05, n), 1.6 - _uniform(g, 0, 12, n))
+        mean, ls, op = torch.stack([x, y, _uniform(g, -50, 50, n)]), _normal(g, -3.5, 0.6, 3, n), _normal(g, 0, 1.5, n)
+    elif scene == "box":
+        mean = torch.stack([_uniform(g, -20, 20, n), _uniform(g, -5, 5, n), _uniform(g, 1, 41, n)])
+        ls, op = _normal(g, -4, 0.5, 3, n), _normal(g, 0, 1.5, n)
+    else:
+        mean = torch.stack([_uniform(g, -1, 1, n), _uniform(g, -1, 1, n), _uniform(g, 2, 6, n)])
+        ls, op = _normal(g, -3, 0.3, 3, n), _normal(g, 0, 1, n)
+    q = _normal(g, 0, 1, 4, n)
+    k = (case.get("degree", 0) + 1) ** 2
+    sh = _normal(g, 0, 0.2, k, 3, n)
+    sh[0] = _uniform(g, 0, 1, 3, n)
+    return dict(mean=mean.contiguous(), log_scale=ls, quat=(q / q.norm(dim=0)).contiguous(), opacity_logit=op, sh=sh)
+
+
+def _moments(params, px, seed):
+    """Adam moments of a run under way: second moments at the size of the gradients of a mean over 3 px values, first moments below them."""
+    g = _gen(seed + 1)
+    size = dict(mean=100.0, log_scale=20.0, quat=10.0, opacity_logit=20.0, sh=10.0)
+    m, v = {}, {}
+    for k in NAMES:
+        s = torch.exp(_normal(g, 0, 0.5, *params[k].shape)) * (size[k] / (3.0 * px))
+        v[k] = s * s
+        m[k] = 0.3 * s * _normal(g, 0, 1, *params[k].shape)
+    return m, v
+
+
+STEP = 200  # optimiser steps already taken
+
+
+def _field(g, w, h):
+    """A photograph-like planar image: smooth shading, flat patches with sharp edges, and fine specks."""
+    y, x = torch.linspace(0, 1, h, device=DEVICE)[:, None], torch.linspace(0, 1, w, device=DEVICE)[None]
+    base = torch.full((3, h, w), 0.5, device=DEVICE)
+    for a in _uniform(g, 0, 1, 4, 5).tolist():
+        base = base + (0.02 + 0.06 * a[0]) * torch.sin(6.28 * (a[1] * 4 * x + a[2] * 4 * y + a[3]))
+    ph, pw = -(-h // 24), -(-w // 24)
+    patch = _uniform(g, -0.5, 0.5, 3, ph, pw) * (torch.rand(1, ph, pw, generator=g, device=DEVICE) < 0.3)
+    detail = patch.repeat_interleave(24, 1).repeat_interleave(24, 2)[:, :h, :w]
+    specks = _normal(g, 0, 0.7, 3, h, w) * (torch.rand(1, h, w, generator=g, device=DEVICE) < 0.01)
+    return base, detail + specks
+
+
+def _images(case, seed, keep=1.0):
+    """One planar image per view, flat one after the other; `keep`: the share of the detail that is there (a render lacks some)."""
+    g = _gen(seed + 2)
+    out = []
+    for w, h in _sizes(case):
+        base, detail = _field(g, w, h)
+        out.append((base + keep * detail).reshape(-1))
+    return torch.cat(out)
+
+
+def _targets(case, seed):
+    t = _images(case, seed)
+    return (t + _uniform(_gen(seed + 3), -0.3, 0.3, t.numel())).clamp_(0, 1)
+
+
+def _depths(case, seed):
+    g = _gen(seed + 4)
+    out = []
+    for w, h in _sizes(case):
+        a = _uniform(g, 0.2, 1.0, 2).tolist()
+        y, x = torch.arange(h, device=DEVICE)[:, None], torch.arange(w, device=DEVICE)[None]
+        out.append((16.5 + 13.5 * torch.sin(6.28 * x / w * a[0]) * torch.cos(6.28 * y / h * a[1])).reshape(-1))
+    return torch.cat(out)
+
+
+def _cotangent(case, seed):
+    px = sum(w * h for w, h in _sizes(case))
+    return _normal(_gen(seed + 5), 0, 1.0 / (3 * px), 3 * px)
+
+
+def _rig(case, seed):
+    """Central poses per frame and relative poses per camera whose products are near the views' poses."""
+    cams = _cameras(case, seed)
+    per, frame, cam = _rig_layout(case["views"])
+    pose = [np.concatenate([c.R.reshape(-1), c.t]).astype(np.float64) for c in cams]
+    central = np.stack([pose[frame.index(f)] for f in range(frame[-1] + 1)])
+    rel = []
+    for k in range(per):
+        m, p = central[0], pose[k]
+        r = m[:9].reshape(3, 3).T @ p[:9].reshape(3, 3)
+        rel.append(np.concatenate([r.reshape(-1), m[:9].reshape(3, 3).T @ (p[9:] - m[9:])]))
+    return (frame, cam, torch.tensor(central, dtype=torch.float32, device=DEVICE),
+            torch.tensor(np.stack(rel), dtype=torch.float32, device=DEVICE))
+
+
+def _schedule_inputs(case, seed):
+    g = _gen(seed + 6)
+    f = case["views"]
+    px = torch.tensor([float(w * h) for w, h in _sizes(case)], device=DEVICE)
+    return dict(x_gt=px * _uniform(g, 60, 200, f), x_gt_level=px * _uniform(g, 20, 120, f), uniforms=_uniform(g, 0, 1, 2 * f),
+                levels=torch.randint(0, 3, (f,), generator=g, device=DEVICE, dtype=torch.int32))
+
+
+def _samples(case, seed):
+    """Sampled pixels of every view, ascending, their probability map, depths along the scene's scale, scales and centres."""
+    g = _gen(seed + 7)
+    sizes, cams, depth = _sizes(case), _cameras(case, seed), _depths(case, seed)
+    px = depth.numel()
+    p = _uniform(g, 0.02, 1.0, px)
+    pix = torch.randperm(px, generator=g, device=DEVICE)[:px // 50].sort().values
+    scale, mean = torch.empty(pix.numel(), device=DEVICE), torch.empty(pix.numel(), 3, device=DEVICE)
+    off = 0
+    for c, (w, h) in zip(cams, sizes):
+        sel = (pix >= off) & (pix < off + w * h)
+        at = pix[sel] - off
+        z = depth[pix[sel]]
+        xc = torch.stack([z * ((at % w) + 0.5 - c.cx) / c.fx, z * (torch.div(at, w, rounding_mode="floor") + 0.5 - c.cy) / c.fy, z], 1)
+        scale[sel] = xc.norm(dim=1) / (2 * p[pix[sel]].sqrt() * c.fx)
+        mean[sel] = (xc - torch.tensor(c.t, device=DEVICE)) @ torch.tensor(c.R, device=DEVICE)
+        off += w * h
+    return dict(p_gt=p, pix=pix.to(torch.int32), scale=scale, mean=mean.contiguous(),
+                count=torch.tensor([pix.numel()], dtype=torch.int32, device=DEVICE))
+
+
+TAU_D = 4.0
+
+
+def _budget(case):
+    """New Gaussians that a program takes from a frame: fewer than there are inserting pixels, so the whole list is written."""
+    return max(1, sum(w * h for w, h in _sizes(case)) // 400)
+
+
+# ------------------------------------------------------------------- running
+
+def _planned(case, cams, params, bg=(0.0, 0.0, 0.0)):
+    """A rasterizer whose capacities a first render has measured, with half as much again to spare."""
+    from paper_2512_08498_amd import Rasterizer
+    kw = dict(tile_size=case["tile"], long_list=case["split"], bg=bg, device=DEVICE)
+    records = max(case["views"] * case["n"] // 4, 1 << 14)
+    r = Rasterizer(cams, case["n"], case["degree"], capacity_records=records, capacity_pairs=6 * records, **kw)
+    r.forward(params)
+    rec, pairs, _ = r.required_capacity()
+    del r
+    return Rasterizer(cams, case["n"], case["degree"], capacity_records=rec * 3 // 2 + 1024, capacity_pairs=pairs * 3 // 2 + 4096, **kw)
+
+
+def prepare(case, seed):
+    from paper_2512_08498_amd import FusedAdam, Rasterizer
+    from paper_2512_08498_amd.frequency import Frequency
+    kind = case["kind"]
+    s = dict(kind=kind)
+    if kind in ("train", "grads", "pose", "render"):
+        cams, params = _cameras(case, seed), _gaussians(case, seed)
+        r = _planned(case, cams, params, (0.2, 0.3, 0.4) if kind == "grads" else (0.0, 0.0, 0.0))
+        s.update(rast=r, params=params)
+        if kind != "grads":
+            s["out"] = r.new_fwd_out()
+        if kind in ("train", "pose"):
+            s.update(target=_targets(case, seed), loss=torch.empty(1, device=DEVICE), dl=torch.empty(3 * r.total_px, device=DEVICE))
+        if kind == "train":
+            s["opt"] = _optimiser(FusedAdam(r, params), params, r.total_px, seed)
+        if kind == "grads":
+            s["leaves"] = {k: v.requires_grad_(True) for k, v in params.items()}
+            s["cotangent"] = _cotangent(case, seed)
+        if kind == "pose":
+            frame, cam, central, relative = _rig(case, seed)
+            r.set_rig(frame, cam, frame[-1] + 1, max(cam) + 1)
+            s.update(central=central, relative=relative, grads={k: torch.empty_like(params[k]) for k in NAMES},
+                     cam_grads=torch.empty(case["views"], 12, device=DEVICE))
+    elif kind == "serve":
+        r = Rasterizer(_cameras(case, seed), case["n"], case["degree"], tile_size=case["tile"], long_list=case["split"], device=DEVICE)
+        s.update(rast=r, params=_gaussians(case, seed), out=r.new_fwd_out())
+    elif kind == "adam":
+        params = _gaussians(case, seed)
+        r = Rasterizer([Cam(np.eye(3, dtype=np.float32), np.zeros(3, np.float32), 60.0, 60.0, 32.0, 24.0, 64, 48)], case["n"], case["degree"],
+                       capacity_records=1024, capacity_pairs=1024, device=DEVICE)
+        s.update(params=params, opt=_optimiser(FusedAdam(r, params), params, 1_000_000, seed), grads=_moments(params, 1_000_000, seed + 8)[0])
+    elif kind == "freq":
+        sizes, d = _sizes(case), case["factor"]
+        s.update(_schedule_inputs(case, seed), freq=Frequency(sizes, device=DEVICE), renders=_images(case, seed, 0.5))
+        if d > 1:
+            small = [(w // d, h // d) for w, h in sizes]
+            s.update(gt=_images(case, seed), level=Frequency(small, device=DEVICE), factor=d,
+                     small=torch.empty(3 * sum(w * h for w, h in small), device=DEVICE))
+    else:
+        r = Rasterizer(_cameras(case, seed), 1, 0, capacity_records=1024, capacity_pairs=1024, device=DEVICE)
+        s.update(rast=r, gt=_images(case, seed))
+        if kind == "insert":
+            s.update(render=_images(case, seed, 0.3), depth=_depths(case, seed), budget=_budget(case))
+        else:
+            s.update(existing=_gaussians(dict(case, scene="street", degree=0), seed), samples=_samples(case, seed))
+            s["merged"] = r.merge(s["existing"], 0, s["gt"], s["samples"], TAU_D)
+    return s
+
+
+def _optimiser(opt, params, px, seed):
+    m, v = _moments(params, px, seed)
+    for k in NAMES:
+        opt.m[k].copy_(m[k])
+        opt.v[k].copy_(v[k])
+    opt.step.fill_(STEP)
+    return opt
+
+
+def run(s):
+    kind = s["kind"]
+    if kind == "train":
+        r = s["rast"]
+        out, loss, dl = r.forward_l1(s["params"], s["target"], s["out"], s["loss"], s["dl"], check=False)
+        r.backward_adam(s["params"], out, dl, s["opt"])
+        return dict(image=out["image"], loss=loss, params=s["params"], m=s["opt"].m, v=s["opt"].v)
+    if kind == "grads":
+        from paper_2512_08498_amd.rasterizer import rasterize
+        image = rasterize(s["rast"], s["leaves"])
+        grads = torch.autograd.grad(image, [s["leaves"][k] for k in NAMES], s["cotangent"])
+        return dict(image=image, grads=dict(zip(NAMES, grads)))
+    if kind == "pose":
+        r = s["rast"]
+        out, loss, dl = r.forward_l1(s["params"], s["target"], s["out"], s["loss"], s["dl"], check=False)
+        grads = r.backward(s["params"], out, dl, grads=s["grads"], cam_grads=s["cam_grads"])
+        return dict(image=out["image"], loss=loss, grads=grads, rig=r.rig_gradients(s["central"], s["relative"], grads["camera"]))
+    if kind in ("render", "serve"):
+        r = s["rast"]
+        out = r.forward(s["params"], out=s["out"], check=False) if kind == "render" else r.forward_noalloc(s["params"], out=s["out"])
+        return dict(image=out["image"], t_final=out["t_final"], n_contrib=out["n_contrib"])
+    if kind == "adam":
+        s["opt"].apply(s["grads"])
+        return dict(params=s["params"], m=s["opt"].m, v=s["opt"].v)
+    if kind == "freq":
+        f, x_level = s["freq"], None
+        if "level" in s:
+            off = at = 0
+            for (w, h), (a, b) in zip(f.sizes, s["level"].sizes):
+                f.downsample(s["gt"][off:off + 3 * w * h], w, h, s["factor"], out=s["small"][at:at + 3 * a * b])
+                off, at = off + 3 * w * h, at + 3 * a * b
+            x_level = s["level"].significance(s["small"])
+        x = f.significance(s["renders"])
+        got = f.schedule(s["x_gt"], x, s["x_gt_level"] if x_level is None else x_level, s["levels"], s["uniforms"])
+        return dict(x=x, x_level=x_level, small=s.get("small"), r=got["r"], r_prime=got["r_prime"], picks=got["picks"], levels=s["levels"])
+    if kind == "insert":
+        return s["rast"].log_insert(s["gt"], s["render"], s["depth"], capacity=s["budget"])
+    return s["rast"].merge(s["existing"], 0, s["gt"], s["samples"], TAU_D, out=s["merged"])
+
+
+# ------------------------------------------------- what a pass cannot do without
+
+def work(case):
+    kind = case["kind"]
+    px = sum(w * h for w, h in _sizes(case)) if "res" in case else 0
+    n = case.get("n", 0)
+    per = 11 + 3 * (case.get("degree", 0) + 1) ** 2  # values of one Gaussian
+    if kind == "adam":
+        return dict(bytes=28 * per * n, flops=12 * per * n)
+    if kind == "freq":
+        # images read once; half spectra by the usual 5/2 N log2 N of a real transform, three channels
+        flops = sum(3 * 2.5 * w * h * math.log2(max(w * h, 2)) for w, h in _sizes(case))
+        if case["factor"] > 1:
+            return dict(bytes=24 * px + 12 * px / case["factor"] ** 2, flops=flops * (1 + 1 / case["factor"] ** 2) + 3 * px)
+        return dict(bytes=12 * px, flops=flops)
+    if kind == "insert":
+        return dict(bytes=28 * px, flops=2 * 3 * 56 * px)  # two images, three channels, 2 x 14 taps
+    if kind == "merge":
+        return dict(bytes=57 * n + 60 * 0.02 * px / case["views"], flops=60 * n)
+    # (pixel, Gaussian) evaluations of the scenes, measured on them, scale with the squared focal length
+    sq = sum(w * w for w, _ in _sizes(case))
+    share, evals = {"street": (0.16, 2.5e-5), "box": (0.5, 1.0e-5), "near": (1.0, 8e-3)}[case["scene"]]
+    evals *= n * sq
+    records = share * n * case["views"]
+    render = 4 * per * n + 48 * records
+    if kind in ("render", "serve"):
+        return dict(bytes=render + 24 * px, flops=24 * evals)
+    step = render + 60 * px + 36 * records
+    return dict(bytes=step + (24 if kind == "train" else 8) * per * n, flops=72 * evals)
+
+
+# ---------------------------------------- the same results in 64 bits, in torch
+
+def _sh_basis(d, degree):
+    x, y, z = d[:, 0], d[:, 1], d[:, 2]
+    pi = math.pi
+    out = [torch.full_like(x, SH0)]
+    if degree >= 1:
+        c = math.sqrt(3 / (4 * pi))
+        out += [-c * y, c * z, -c * x]
+    if degree >= 2:
+        a, b = math.sqrt(15 / pi) / 2, math.sqrt(5 / pi) / 4
+        out += [a * x * y, -a * y * z, b * (2 * z * z - x * x - y * y), -a * x * z, a / 2 * (x * x - y * y)]
+    if degree >= 3:
+        a, b, c, d3 = math.sqrt(35 / (2 * pi)) / 4, math.sqrt(105 / pi) / 2, math.sqrt(21 / (2 * pi)) / 4, math.sqrt(7 / pi) / 4
+        out += [-a * y * (3 * x * x - y * y), b * x * y * z, -c * y * (4 * z * z - x * x - y * y), d3 * z * (2 * z * z - 3 * x * x - 3 * y * y),
+                -c * x * (4 * z * z - x * x - y * y), b / 2 * z * (x * x - y * y), -a * x * (x * x - 3 * y * y)]
+    return torch.stack(out, 1)
+
+
+def _cam64(c):
+    return (torch.tensor(c.R, dtype=torch.float64, device=DEVICE), torch.tensor(c.t, dtype=torch.float64, device=DEVICE))
+
+
+def _project64(p, degree, c, R, t):
+    """2D mean, conic, opacity, colour and covariance of Gaussians p ([.., m] arrays in 64 bits) in the view c with pose R, t."""
+    w, x, y, z = (p["quat"] / p["quat"].norm(dim=0)).unbind(0)
+    rot = torch.stack([1 - 2 * (y * y + z * z), 2 * (x * y - w * z), 2 * (x * z + w * y), 2 * (x * y + w * z), 1 - 2 * (x * x + z * z),
+                       2 * (y * z - w * x), 2 * (x * z - w * y), 2 * (y * z + w * x), 1 - 2 * (x * x + y * y)], 1).reshape(-1, 3, 3)
+    M = rot * p["log_scale"].exp().T[:, None, :]
+    xc = p["mean"].T @ R.T + t
+    X, Y, Z = xc.unbind(1)
+    lx, ly = 1.3 * max(c.cx, c.width - c.cx) / c.fx, 1.3 * max(c.cy, c.height - c.cy) / c.fy
+    o = torch.zeros_like(Z)
+    J = torch.stack([torch.stack([c.fx / Z, o, -c.fx * (X / Z).clamp(-lx, lx) / Z], 1),
+                     torch.stack([o, c.fy / Z, -c.fy * (Y / Z).clamp(-ly, ly) / Z], 1)], 1)
+    A = J @ R @ M
+    S = A @ A.transpose(1, 2)
+    sxx, sxy, syy = S[:, 0, 0] + 0.3, S[:, 0, 1], S[:, 1, 1] + 0.3
+    det = sxx * syy - sxy * sxy
+    R0, t0 = _cam64(c)  # the viewing direction is not part of a pose's gradient
+    d = p["mean"].T + (R0.T @ t0)
+    d = d / d.norm(dim=1, keepdim=True)
+    rgb = (torch.einsum("mk,kcm->mc", _sh_basis(d, degree), p["sh"]) + 0.5).clamp_min(0)
+    return dict(mu=torch.stack([c.fx * X / Z + c.cx, c.fy * Y / Z + c.cy], 1), conic=torch.stack([syy / det, -sxy / det, sxx / det], 1),
+                op=torch.sigmoid(p["opacity_logit"]), rgb=rgb), sxx, syy
+
+
+def _render64(p32, degree, cams, bg, cotangent=None):
+    """Image and transmittance of all views, and the gradients for the cotangent(image); brute force over 16 px tiles, all tiles at once."""
+    p = {k: v.detach().double() for k, v in p32.items()}
+    n = p["mean"].shape[1]
+    recs, tiles, depths, pix = [], [], [], [0]
+    base, m32 = 0, p32["mean"].detach()
+    for c in cams:
+        R, t = _cam64(c)
+        r32 = [float(v) for v in c.R.reshape(-1)]
+        z = ((m32[0] * r32[6] + m32[1] * r32[7]) + m32[2] * r32[8]) + float(c.t[2])  # the sort key, in 32 bits
+        front = torch.nonzero(z > 0.2).reshape(-1)
+        q, sxx, syy = _project64({k: v[..., front] for k, v in p.items()}, degree, c, R, t)
+        hx, hy = (11.0826 * sxx).sqrt(), (11.0826 * syy).sqrt()
+        u, v = q["mu"].unbind(1)
+        lo_x, hi_x = torch.ceil(u - hx - 0.5).clamp(-1, c.width), torch.floor(u + hx - 0.5).clamp(-1, c.width)
+        lo_y, hi_y = torch.ceil(v - hy - 0.5).clamp(-1, c.height), torch.floor(v + hy - 0.5).clamp(-1, c.height)
+        ok = (lo_x <= hi_x) & (lo_y <= hi_y) & (hi_x >= 0) & (lo_x < c.width) & (hi_y >= 0) & (lo_y < c.height)
+        tx = [torch.div(e.clamp(0, c.width - 1), 16, rounding_mode="floor").long()[ok] for e in (lo_x, hi_x)]
+        ty = [torch.div(e.clamp(0, c.height - 1), 16, rounding_mode="floor").long()[ok] for e in (lo_y, hi_y)]
+        across = -(-c.width // 16)
+        recs.append(dict({k: e[ok] for k, e in q.items()}, g=front[ok], tx=tx, ty=ty, base=base, across=across))
+        depths.append(z[front[ok]])
+        tiles.append((base, across, c.width, c.height))
+        base += across * -(-c.height // 16)
+        pix.append(pix[-1] + c.width * c.height)
+    cat = {k: torch.cat([r[k] for r in recs]) for k in ("mu", "conic", "op", "rgb")}
+    first = np.cumsum([0] + [len(r["g"]) for r in recs])
+    # (tile, record) pairs in (tile, depth, index) order
+    pair_tile, pair_rec, key = [], [], []
+    for i, r in enumerate(recs):
+        w = r["tx"][1] - r["tx"][0] + 1
+        count = w * (r["ty"][1] - r["ty"][0] + 1)
+        rec = torch.repeat_interleave(torch.arange(len(w), device=DEVICE), count)
+        k = torch.arange(len(rec), device=DEVICE) - (count.cumsum(0) - count)[rec]
+        pair_tile.append(r["base"] + (r["ty"][0][rec] + torch.div(k, w[rec], rounding_mode="floor")) * r["across"] + r["tx"][0][rec] + k % w[rec])
+        order = torch.sort(depths[i], stable=True).indices  # records keep the Gaussians' order
+        rank = torch.empty_like(order)
+        rank[order] = torch.arange(len(order), device=DEVICE)
+        pair_rec.append(rec + int(first[i]))
+        key.append(rank[rec])
+    pair_tile, pair_rec, key = torch.cat(pair_tile), torch.cat(pair_rec), torch.cat(key)
+    by = torch.sort(pair_tile * (int(key.max()) + 1 if len(key) else 1) + key).indices
+    pair_tile, pair_rec = pair_tile[by], pair_rec[by]
+    count = torch.bincount(pair_tile, minlength=base)
+    start = count.cumsum(0) - count
+    tile = torch.sort(count, descending=True, stable=True).indices  # longest lists first: step k works on a prefix
+    count, start = count[tile], start[tile]
+    active = [int(a) for a in torch.bincount(count).flip(0).cumsum(0).flip(0)[1:]] if len(pair_tile) else []
+    px, py, at, inside = (torch.empty(base, 256, dtype=d, device=DEVICE) for d in (torch.float64, torch.float64, torch.long, torch.bool))
+    ii = torch.arange(256, device=DEVICE)
+    for v, (b, across, w, h) in enumerate(tiles):
+        sel = torch.nonzero((tile >= b) & (tile < (tiles[v + 1][0] if v + 1 < len(tiles) else base))).reshape(-1)
+        lt = tile[sel] - b
+        x, y = (lt % across * 16)[:, None] + ii % 16, (torch.div(lt, across, rounding_mode="floor") * 16)[:, None] + ii // 16
+        px[sel], py[sel], inside[sel] = x.double() + 0.5, y.double() + 0.5, (x < w) & (y < h)
+        at[sel] = 3 * pix[v] + y.clamp(max=h - 1) * w + x.clamp(max=w - 1)  # place in the flat image, channel 0
+    plane = torch.empty(base, dtype=torch.long, device=DEVICE)
+    for v, (b, across, w, h) in enumerate(tiles):
+        plane[(tile >= b)] = w * h
+
+    def evaluate(k, a):
+        rec = pair_rec[start[:a] + k]
+        mu, con = cat["mu"][rec], cat["conic"][rec]
+        dx, dy = px[:a] - mu[:, :1], py[:a] - mu[:, 1:]
+        e = torch.exp(-0.5 * (con[:, :1] * dx * dx + con[:, 2:] * dy * dy) - con[:, 1:2] * dx * dy)
+        return rec, dx, dy, e, cat["op"][rec][:, None] * e
+
+    T = torch.ones(base, 256, dtype=torch.float64, device=DEVICE)
+    C = [torch.zeros_like(T) for _ in range(3)]
+    last = torch.zeros(base, 256, dtype=torch.int32, device=DEVICE)
+    done = torch.zeros_like(inside)
+    for k, a in enumerate(active):
+        rec, _, _, _, raw = evaluate(k, a)
+        alpha = raw.clamp(max=0.99)
+        hit = (alpha >= 1 / 255) & ~done[:a]
+        tn = T[:a] * (1 - alpha)
+        stop = hit & (tn < 1e-4)
+        done[:a] |= stop
+        comp = hit & ~stop
+        wgt = torch.where(comp, alpha * T[:a], 0.0)
+        for ch in range(3):
+            C[ch][:a] += wgt * cat["rgb"][rec, ch][:, None]
+        T[:a] = torch.where(comp, tn, T[:a])
+        last[:a] = torch.where(comp, k + 1, last[:a])
+    image = torch.empty(3 * pix[-1], dtype=torch.float64, device=DEVICE)
+    t_final = torch.empty(pix[-1], dtype=torch.float64, device=DEVICE)
+    for ch in range(3):
+        image[(at + ch * plane[:, None])[inside]] = (C[ch] + T * bg[ch])[inside]
+    for v, (b, across, w, h) in enumerate(tiles):
+        sel = (tile >= b) & (tile < (tiles[v + 1][0] if v + 1 < len(tiles) else base))
+        t_final[(at[sel] - 2 * pix[v])[inside[sel]]] = T[sel][inside[sel]]
+    if cotangent is None:
+        return image, t_final, None, None
+    dC = cotangent(image)
+    g = [torch.where(inside, dC[at + ch * plane[:, None]], 0.0) for ch in range(3)]
+    S = sum(g[ch] * bg[ch] for ch in range(3))
+    d_rec = torch.zeros(len(cat["op"]), 9, dtype=torch.float64, device=DEVICE)
+    for k in range(len(active) - 1, -1, -1):
+        a = active[k]
+        rec, dx, dy, e, raw = evaluate(k, a)
+        alpha = torch.where((last[:a] > k) & (raw >= 1 / 255), raw.clamp(max=0.99), 0.0)
+        ti = T[:a] / (1 - alpha)
+        T[:a] = ti
+        wgt = alpha * ti
+        cg = sum(g[ch][:a] * cat["rgb"][rec, ch][:, None] for ch in range(3))
+        dla = torch.where((alpha > 0) & (raw <= 0.99), ti * (cg - S[:a]), 0.0)
+        S[:a] += alpha * (cg - S[:a])
+        con, dp = cat["conic"][rec], dla * raw  # dL/d(exponent)
+        gx, gy = dp * (con[:, :1] * dx + con[:, 1:2] * dy), dp * (con[:, 2:] * dy + con[:, 1:2] * dx)
+        d_rec.index_add_(0, rec, torch.stack([gx.sum(1), gy.sum(1), (-0.5 * dp * dx * dx).sum(1), (-dp * dx * dy).sum(1),
+                                              (-0.5 * dp * dy * dy).sum(1), (dla * e).sum(1)] + [(wgt * g[ch][:a]).sum(1) for ch in range(3)], 1))
+    grads = {k: torch.zeros_like(v) for k, v in p.items()}
+    pose = []
+    for i, (c, r) in enumerate(zip(cams, recs)):
+        sub = {k: v[..., r["g"]].clone().requires_grad_(True) for k, v in p.items()}
+        R, t = (e.requires_grad_(True) for e in _cam64(c))
+        q = _project64(sub, degree, c, R, t)[0]
+        d = d_rec[int(first[i]):int(first[i + 1])]
+        got = torch.autograd.grad([q["mu"], q["conic"], q["op"], q["rgb"]], list(sub.values()) + [R, t], [d[:, 0:2], d[:, 2:5], d[:, 5], d[:, 6:9]])
+        for k, e in zip(sub, got):
+            grads[k].index_add_(-1, r["g"], e)
+        pose.append(torch.cat([got[-2].reshape(-1), got[-1]]))
+    return image, t_final, grads, torch.stack(pose)
+
+
+def _adam64(params, grads, m, v):
+    t = STEP + 1
+    out = (dict(), dict(), dict())
+    for k in NAMES:
+        p, g = params[k].double(), grads[k].double()
+        m1, v1 = 0.9 * m[k].double() + 0.1 * g, 0.999 * v[k].double() + 0.001 * g * g
+        lr = torch.full_like(p, LR[NAMES.index(k)])
+        if k == "sh":
+            lr[1:] = LR[5]
+        out[0][k] = p - lr * (m1 / (1 - 0.9 ** t)) / ((v1 / (1 - 0.999 ** t)).sqrt() + 1e-15)
+        out[1][k], out[2][k] = m1, v1
+    return out
+
+
+def _left_tangent(T, G):
+    R, D = T[:9].reshape(3, 3), G[:9].reshape(3, 3)
+    return torch.cat([G[9:], torch.linalg.cross(R, D, dim=0).sum(1) + torch.linalg.cross(T[9:], G[9:], dim=0)])
+
+
+def _rig64(case, seed, view_grads):
+    frame, cam, central, relative = _rig(case, seed)
+    c, r = central.double(), relative.double()
+    dc, dr = torch.zeros_like(c), torch.zeros_like(r)
+    for v, (f, k) in enumerate(zip(frame, cam)):
+        G, g = view_grads[v, :9].reshape(3, 3), view_grads[v, 9:]
+        Rm, Rr = c[f, :9].reshape(3, 3), r[k, :9].reshape(3, 3)
+        dc[f] += torch.cat([(G @ Rr.T + torch.outer(g, r[k, 9:])).reshape(-1), g])
+        dr[k] += torch.cat([(Rm.T @ G).reshape(-1), Rm.T @ g])
+    return dict(d_central=dc, d_relative=dr, xi_central=torch.stack([_left_tangent(a, b) for a, b in zip(c, dc)]),
+                xi_relative=torch.stack([_left_tangent(a, b) for a, b in zip(r, dr)]))
+
+
+def _probability64(image, w, h):
+    x = torch.arange(-3, 4, dtype=torch.float64, device=DEVICE)
+    g = torch.exp(-x * x / 2)
+    g = g / g.sum()
+    d = (x * x - 1) * g
+    d = d - d.mean()
+    d = d * 2 / (x * x * d).sum()
+    img = image.double().reshape(3, h, w)
+    rows = torch.cat([img[:, :, :1].expand(-1, -1, 3), img, img[:, :, -1:].expand(-1, -1, 3)], 2)
+    full = torch.cat([rows[:, :1].expand(-1, 3, -1), rows, rows[:, -1:].expand(-1, 3, -1)], 1)
+    out = torch.zeros_like(img)
+    for j in range(7):
+        for i in range(7):
+            out += (g[j] * d[i] + d[j] * g[i]) * full[:, j:j + h, i:i + w]
+    return out.square().sum(0).sqrt().clamp(max=1)
+
+
+def _merge64(case, seed):
+    e, s, c, (w, h) = _gaussians(dict(case, scene="street", degree=0), seed), _samples(case, seed), _cameras(case, seed)[0], _sizes(case)[0]
+    gt = _images(case, seed)[:3 * w * h].double().reshape(3, -1)
+    R, t = _cam64(c)
+    mean, pix = e["mean"].double(), s["pix"].long()
+    k = pix[pix < w * h]  # view 0's samples come first
+    cen = s["mean"][:len(k)].double()
+    xc = mean.T @ R.T + t
+    d, z = xc.norm(dim=1), xc[:, 2]
+    zs = torch.where(z > 0.2, z, 1.0)
+    u, v = c.fx * xc[:, 0] / zs + c.cx, c.fy * xc[:, 1] / zs + c.cy
+    ok = (z > 0.2) & (u >= 0) & (u < w) & (v >= 0) & (v < h)
+    i0, j0 = torch.floor(u - 0.5), torch.floor(v - 0.5)
+    al, be = u - 0.5 - i0, v - 0.5 - j0
+    slot = torch.full((w * h,), -1, dtype=torch.long, device=DEVICE)
+    slot[k] = torch.arange(len(k), device=DEVICE)
+    best, match, P = torch.zeros_like(u), torch.full_like(k[:1], -1).expand(len(u)).clone(), torch.zeros_like(u)
+    for q in range(4):
+        i, j = (i0 + q % 2).long(), (j0 + q // 2).long()
+        wt = (al if q % 2 else 1 - al) * (be if q // 2 else 1 - be)
+        place = j.clamp(0, h - 1) * w + i.clamp(0, w - 1)
+        P += wt * s["p_gt"][place].double()
+        m = torch.where((i >= 0) & (i < w) & (j >= 0) & (j < h) & ok & (wt > best), slot[place], -1)
+        best, match = torch.where(m >= 0, wt, best), torch.where(m >= 0, m, match)
+    ds = (cen @ R.T + t).norm(dim=1)
+    match = torch.where((match >= 0) & ((d - ds[match.clamp(min=0)]).abs() <= TAU_D), match, -1)
+    rho = (e["log_scale"].double().mean(0).exp() * c.fx / d * 2 * P.clamp(min=0).sqrt()).float()
+    has = torch.nonzero(match >= 0).reshape(-1)
+    mk, one = match[has], torch.ones(len(has), dtype=torch.float64, device=DEVICE)
+    count = torch.zeros(len(k), dtype=torch.float64, device=DEVICE).index_add_(0, mk, one)
+    low = torch.full((len(k),), math.inf, device=DEVICE).scatter_reduce_(0, mk, rho[has], "amin")
+    tied = has[rho[has] == low[mk]]
+    win = torch.full((len(k),), 1 << 40, device=DEVICE).scatter_reduce_(0, match[tied], tied, "amin")
+    old = low <= 1
+    own, new = SH0 * e["sh"][0].double() + 0.5, gt[:, k]
+    colour = (torch.zeros_like(new).index_add_(1, mk, own[:, has]) + new) / (count + 1)
+    dist = (torch.zeros_like(ds).index_add_(0, mk, d[has]) + ds) / (count + 1)
+    centre = -(R.T @ t)
+    winners = torch.nonzero(old).reshape(-1)
+    gw = win[winners]
+    colour_out, mean_out = own.clone(), mean.clone()
+    colour_out[:, gw] = colour[:, winners]
+    mean_out[:, gw] = centre[:, None] + (mean[:, gw] - centre[:, None]) * (dist[winners] / d[gw])
+    merged = (count > 0) & ~old
+    total = len(pix)
+    colour_new, mean_new = torch.zeros(total, 3, dtype=torch.float64, device=DEVICE), torch.zeros(total, 3, dtype=torch.float64, device=DEVICE)
+    colour_new[:len(k)] = torch.where(merged, colour, new).T
+    mean_new[:len(k)] = torch.where(merged[:, None], centre + (cen - centre) * (dist / ds)[:, None], cen)
+    return dict(keep=None, colour=colour_out, mean=mean_out, keep_new=None, colour_new=colour_new, mean_new=mean_new)
+
+
+def exact(case, seed):
+    kind = case["kind"]
+    if kind == "adam":
+        params = _gaussians(case, seed)
+        m, v = _moments(params, 1_000_000, seed)
+        p, m, v = _adam64(params, _moments(params, 1_000_000, seed + 8)[0], m, v)
+        return dict(params=p, m=m, v=v)
+    if kind == "freq":
+        sizes, d, x, x_level, small = _sizes(case), case["factor"], [], [], []
+
+        def significance(image):
+            return torch.fft.fft2(image.double()).abs().square().sum(0).sqrt().sum()
+
+        off, renders, gt = 0, _images(case, seed, 0.5), _images(case, seed) if d > 1 else None
+        for w, h in sizes:
+            x.append(significance(renders[off:off + 3 * w * h].reshape(3, h, w)))
+            if d > 1:
+                part = gt[off:off + 3 * w * h].double().reshape(3, h, w)[:, :h // d * d, :w // d * d]
+                small.append(part.reshape(3, h // d, d, w // d, d).mean((2, 4)))
+                x_level.append(significance(small[-1]))
+            off += 3 * w * h
+        s, x = _schedule_inputs(case, seed), torch.stack(x)
+        level = torch.stack(x_level) if d > 1 else s["x_gt_level"].double()
+        return dict(x=x, x_level=level if d > 1 else None, small=torch.cat([e.reshape(-1) for e in small]) if d > 1 else None,
+                    r=s["x_gt"].double() / x, r_prime=level / x, picks=None, levels=None)
+    if kind == "insert":
+        gt, rd, z, off = _images(case, seed), _images(case, seed, 0.3), _depths(case, seed).double(), 0
+        p_gt, scale, mean, near = [], [], [], math.inf
+        for c, (w, h) in zip(_cameras(case, seed), _sizes(case)):
+            p, q = (_probability64(e[3 * off:3 * (off + w * h)], w, h).reshape(-1) for e in (gt, rd))
+            at = torch.nonzero((p - q).clamp(min=0) > float(np.float32(0.2))).reshape(-1)
+            near = min(near, float((p - q - 0.2).abs().min()))
+            d = z[off:off + w * h][at]
+            xc = torch.stack([d * ((at % w) + 0.5 - c.cx) / c.fx, d * (torch.div(at, w, rounding_mode="floor") + 0.5 - c.cy) / c.fy, d], 1)
+            R, t = _cam64(c)
+            p_gt.append(p)
+            scale.append(xc.norm(dim=1) / (2 * p[at].sqrt() * c.fx))
+            mean.append((xc - t) @ R)
+            off += w * h
+        known = near > 1e-6  # else 32 bits may list a pixel more or less, and every later place moves
+        return dict(p_gt=torch.cat(p_gt), p_render=None, pix=None, scale=torch.cat(scale)[:_budget(case)] if known else None,
+                    mean=torch.cat(mean)[:_budget(case)] if known else None, count=None)
+    if kind == "merge":
+        return _merge64(case, seed)
+    if case["n"] * case["views"] > 16_000_000:  # minutes of list steps and tens of GB
+        return None
+    cams, params = _cameras(case, seed), _gaussians(case, seed)
+    if kind in ("render", "serve"):
+        image, t_final, _, _ = _render64(params, case["degree"], cams, (0.0, 0.0, 0.0))
+        return dict(image=image, t_final=t_final, n_contrib=None)
+    if kind == "grads":
+        image, _, grads, _ = _render64(params, case["degree"], cams, (0.2, 0.3, 0.4), lambda im: _cotangent(case, seed).double())
+        return dict(image=image, grads=grads)
+    target = _targets(case, seed).double()
+    image, _, grads, pose = _render64(params, case["degree"], cams, (0.0, 0.0, 0.0), lambda im: torch.sign(im - target) / im.numel())
+    loss = (image - target).abs().mean().reshape(1)
+    if kind == "pose":
+        return dict(image=image, loss=loss, grads=dict(grads, camera=pose), rig=_rig64(case, seed, pose))
+    m, v = _moments(params, target.numel() // 3, seed)
+    p, m, v = _adam64(params, grads, m, v)
+    return dict(image=image, loss=loss, params=p, m=m, v=v)
