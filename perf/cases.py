@@ -19,7 +19,8 @@ import torch
 DEVICE = "cuda" if torch.cuda.is_available() else "cpu"
 NEVER = 0xFFFFFFFF  # long-list split that no tile reaches
 SH0 = 0.28209479177387814
-LR = (1.6e-4, 5e-3, 1e-3, 5e-2, 2.5e-3, 2.5e-3 / 20.0)  # the optimiser's defaults
+# the optimiser's default rates at the end of their decay: the scene stays what it is over the many passes that a measurement takes
+LR = tuple(2e-4 * x for x in (1.6e-4, 5e-3, 1e-3, 5e-2, 2.5e-3, 2.5e-3 / 20.0))
 NAMES = ("mean", "log_scale", "quat", "opacity_logit", "sh")
 
 Cam = collections.namedtuple("Cam", "R t fx fy cx cy width height")
@@ -298,7 +299,7 @@ def prepare(case, seed):
         if kind in ("train", "pose"):
             s.update(target=_targets(case, seed), loss=torch.empty(1, device=DEVICE), dl=torch.empty(3 * r.total_px, device=DEVICE))
         if kind == "train":
-            s["opt"] = _optimiser(FusedAdam(r, params), params, r.total_px, seed)
+            s["opt"] = _optimiser(FusedAdam(r, params, lr=LR), params, r.total_px, seed)
         if kind == "grads":
             s["leaves"] = {k: v.requires_grad_(True) for k, v in params.items()}
             s["cotangent"] = _cotangent(case, seed)
@@ -314,7 +315,7 @@ def prepare(case, seed):
         params = _gaussians(case, seed)
         r = Rasterizer([Cam(np.eye(3, dtype=np.float32), np.zeros(3, np.float32), 60.0, 60.0, 32.0, 24.0, 64, 48)], case["n"], case["degree"],
                        capacity_records=1024, capacity_pairs=1024, device=DEVICE)
-        s.update(params=params, opt=_optimiser(FusedAdam(r, params), params, 1_000_000, seed), grads=_moments(params, 1_000_000, seed + 8)[0])
+        s.update(params=params, opt=_optimiser(FusedAdam(r, params, lr=LR), params, 1_000_000, seed), grads=_moments(params, 1_000_000, seed + 8)[0])
     elif kind == "freq":
         sizes, d = _sizes(case), case["factor"]
         s.update(_schedule_inputs(case, seed), freq=Frequency(sizes, device=DEVICE), renders=_images(case, seed, 0.5))
