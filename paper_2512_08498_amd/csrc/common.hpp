@@ -53,9 +53,9 @@ struct Ws {
   uint32_t *rec_zbits;      // [cap_rec] depth bits
   uint32_t *rec_tmp;        // [5][cap_rec] depth sort of the records, pair offsets
   uint32_t *tile_order;     // [T_tot] tiles by decreasing list length
-  uint32_t *tile_tmp;       // [4][T_tot] keys and values of the tile-order sort
-  uint32_t *radix_hist;     // [radix][blocks] digit histograms of the counting passes (radix <= 1024)
-  uint32_t *scan_part;      // chunk sums of the device-wide scans
+  uint32_t *tile_tmp;       // [2][T_tot] longest-first codes of the tiles, and the fallback order's unused keys
+  uint32_t *radix_hist;     // [blocks][256] code counts of the tile order; [radix][chunks] of the fallback order
+  uint32_t *scan_part;      // digit totals of a counting pass; chunk sums of the emission and of the CSR scan
   uint32_t *pairs_tmp;      // [2][cap_pairs] tile ids and records of the tile sort
   uint32_t *tile_recs;      // [cap_pairs] record list of every tile, in depth order
   float *partials;          // [cap_pairs][9] backward partial gradients per pair, 36 bytes each

@@ -63,6 +63,11 @@ void launch_zero(uint32_t *p, uint64_t n_words, hipStream_t st);
 void launch_preprocess(const GaussPtrs &gp, const Cam *cams, const ViewInfo *views, const Ws &ws,
                        const Sizes &sz, int sh_degree, uint32_t *zero, uint64_t n_zero, hipStream_t st);
 void launch_depth_sort(const Ws &ws, const Sizes &sz, hipStream_t st);
+// Words of the binning's shared scratch under the plan `sz`.
+struct BinningScratch {
+  size_t radix_hist, scan_part;
+};
+BinningScratch binning_scratch(const Sizes &sz);
 void launch_binning(const ViewInfo *views, const Ws &ws, const Sizes &sz, hipStream_t st);
 void launch_tile_csr(const Ws &ws, const Sizes &sz, uint32_t *csr, hipStream_t st);
 void launch_raster_fwd(const ViewInfo *views, const Ws &ws, const Sizes &sz, float *image, float *t_final,

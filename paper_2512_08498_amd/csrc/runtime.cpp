@@ -141,11 +141,6 @@ Layout make_layout(const Sizes &s) {
     field = o;
     o = align_up(o + bytes);
   };
-  // counting passes of the binning: at least 2048 items per block, 256
-  // digits; the device-wide scans take 4096 words per chunk
-  const size_t items = std::max<size_t>(std::max<size_t>(s.cap_pairs, s.cap_rec), s.t_tot);
-  const size_t radix_blocks = std::max<size_t>((items + 2047) / 2048, 1);
-  const size_t scan_words = std::max<size_t>(std::max<size_t>(1024 * radix_blocks, s.cap_rec), (size_t)s.t_tot + 1);
   put(L.scalars, kNumScalars * 4);
   put(L.queues, 2 * kQueueLanes * kQueueStride * 4);
   put(L.tile_count, (size_t)s.t_tot * 4);
@@ -162,9 +157,10 @@ Layout make_layout(const Sizes &s) {
   put(L.rec_zbits, (size_t)s.cap_rec * 4);
   put(L.rec_tmp, (size_t)s.cap_rec * 20);
   put(L.tile_order, (size_t)s.t_tot * 4);
-  put(L.tile_tmp, (size_t)s.t_tot * 16);
-  put(L.radix_hist, 1024 * radix_blocks * 4);
-  put(L.scan_part, (scan_words + 4095) / 4096 * 4);
+  put(L.tile_tmp, (size_t)s.t_tot * 8);
+  const BinningScratch bs = binning_scratch(s);
+  put(L.radix_hist, bs.radix_hist * 4);
+  put(L.scan_part, bs.scan_part * 4);
   put(L.pairs_tmp, (size_t)s.cap_pairs * 8);
   put(L.tile_recs, (size_t)s.cap_pairs * 4);
   // per-pair partials (36 bytes); the pose gradients reuse them afterwards
