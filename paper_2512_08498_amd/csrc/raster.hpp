@@ -1,16 +1,13 @@
 // Tile geometry shared by the forward and backward compositing kernels.
 //
-// A tile of TS x TS pixels is walked by one workgroup, or at 16 px by one
-// wave of it: one workgroup per work item, or (a tuning option) persistent
+// The forward walks a tile with a wave per 8 x 8 block (raster_fwd.hip); the
+// backward with one workgroup, or at 16 px with one wave of it: one workgroup per work item, or (a tuning option) persistent
 // workgroups taking items from a work queue.  Records are staged in LDS in
 // batches and read back as broadcasts; per 8 x 8 pixel block a wave visits
-// only the records whose box (in the forward, whose falloff) can reach it
-// (block_masks), so a record that misses a block costs nothing there.  The
-// forward and the
-// backward split a tile differently (FwdTile / TileCfg below): the forward
-// spreads a tile over four waves (one pixel per lane), the backward keeps a
-// 16 x 16 block in one wave (four pixels per lane) so the per-record wave
-// reduction is paid once per block.  Tiles are visited longest list first.
+// only the records whose box can reach it (block_masks), so a record that
+// misses a block costs nothing there.  The backward keeps a 16 x 16 block in
+// one wave (four pixels per lane) so the per-record wave reduction is paid
+// once per block (TileCfg below).  Tiles are visited longest list first.
 //
 // Per pixel and Gaussian, with the record's payload (see common.hpp):
 //   dx = (px - i0) - offx,  dy = (py - j0) - offy
@@ -144,33 +141,6 @@ __device__ __forceinline__ uint32_t compact_slot(bool keep, uint32_t *wc, uint32
   }
   total = tot;
   return off + before;
-}
-
-// Forward at 8 and 32 px (and for long lists at 16 px): all waves of the
-// workgroup share the tile's LDS batch, each wave an 8 x 8 block with one
-// pixel per lane (four pixels per lane, one per 16 x 16 quadrant, at
-// TS = 32).  Sharing a tile over four waves shortens the critical path of
-// long lists.
-template <int TS>
-struct FwdTile {
-  static constexpr int NT = TS == 8 ? 64 : 256;
-  static constexpr int PPT = TS == 32 ? 4 : 1;
-};
-
-template <int TS>
-__device__ __forceinline__ void fwd_pixel(int t, int p, int &x, int &y) {
-  const int l = t & 63, w = t >> 6;
-  if (TS == 8) {
-    x = l & 7;
-    y = l >> 3;
-  } else {
-    x = (w & 1) * 8 + (l & 7);
-    y = (w >> 1) * 8 + (l >> 3);
-    if (TS == 32) {
-      x += (p & 1) * 16;
-      y += (p >> 1) * 16;
-    }
-  }
 }
 
 // Backward: one wave per 16 x 16 block with four pixels per lane, so the
