@@ -127,7 +127,7 @@ extern "C" gsr_status gsr_autotune(gsr_ctx *c, const gsr_gaussians *g, const gsr
 
   std::vector<gsr_tuning> candidates;
   for (int pers = 0; pers < 2; ++pers) {
-    for (uint32_t ll : {1024u, 512u, 256u, 0u, 0xFFFFFFFFu}) candidates.push_back({16, ll, pers, 0.f});
+    for (uint32_t ll : {1024u, 0u}) candidates.push_back({16, ll, pers, 0.f});
     candidates.push_back({8, 512u, pers, 0.f});
     candidates.push_back({32, 512u, pers, 0.f});
   }

@@ -681,10 +681,21 @@ __global__ void k_tile_bounds(Ws ws, Sizes sz, const uint32_t *__restrict__ tile
 
 // 3b. Per tile the list bounds, the longest-first code and, per block of
 // kOrderNT tiles, the code histogram (codes of 8 bits) and the number of
-// lists of at least long_list entries.  The bounds come from k_tile_bounds,
+// long lists.  The bounds come from k_tile_bounds,
 // or (SEARCH) from a binary search for each tile's first sorted entry: on 67M
 // pairs the search takes 37 us and the pass over them 63, on 4.3M 17 and 10.
 constexpr int kOrderNT = 1024;
+// A list is long (the backward walks it with a wave per 8 x 8 block, see
+// raster_bwd.hip) from a share of all pairs, where it would outlast the rest:
+// one wave takes about five times as long per entry alone as it does among
+// five others, so a list of a 5000th of all pairs takes as long as the 1024
+// SIMDs do for everything.  Measured at shares of 2048, 4096, 8192 and 16384:
+// four views of the rig 520, 520, 543 and 589 us, one 1080p view of 500k 158,
+// 162, 176 and 181, four 800x450 views of 100k 107, 105, 105 and 106 (271
+// without).  A fixed length does not carry over: from 512 and 1024 entries
+// the whole rig takes 661 and 626 us (626 with the share), 40 mixed views 7.5
+// ms from 1024 (6.5).  long_list below kLongMin is taken as it is.
+constexpr uint32_t kLongShare = 4096, kLongMin = 32;
 
 __device__ __forceinline__ uint32_t lower_bound(const uint32_t *__restrict__ a, uint32_t n, uint32_t x) {
   uint32_t lo = 0;
@@ -726,7 +737,8 @@ __global__ __launch_bounds__(kOrderNT) void k_tile_ranges(Ws ws, Sizes sz, const
     codes[tile] = code;
     atomicAdd(&h[code], 1u);
   }
-  (void)wave_atomic_inc(ws.scalars + kNumLong, valid && len >= sz.long_list);
+  const uint32_t long_len = sz.long_list < kLongMin ? sz.long_list : max(kLongMin, ws.scalars[kNumPairs] / kLongShare);
+  (void)wave_atomic_inc(ws.scalars + kNumLong, valid && len >= long_len);
   __syncthreads();
   if (t < 256) code_hist[(size_t)blockIdx.x * 256 + t] = h[t];
 }

@@ -72,7 +72,7 @@ struct Sizes {
   uint32_t cap_rec;
   uint32_t cap_pairs;
   uint32_t n_blocks;        // ceil(n / kPreBlock)
-  uint32_t long_list;       // 16 px tiles: lists this long are walked by four waves in the backward
+  uint32_t long_list;       // gsr_tuning.long_list: which 16 px lists take a wave per 8 x 8 block (k_tile_ranges)
   uint32_t persistent;      // compositing: 1 = persistent workgroups over a work queue (ItemQueue)
   uint32_t vis_words;       // ceil(n_views / 64)
   float bg[3];

@@ -35,6 +35,7 @@ __global__ __launch_bounds__(256) void k_cam_reduce(const float4 *__restrict__ c
   const uint32_t base = blockIdx.x * kCamChunk;
   if (base >= nrec) return;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int mine = sum9_value(lane);
   uint32_t vw[kCamPer];
   float4 x[kCamPer][3];
 #pragma unroll
@@ -72,9 +73,8 @@ __global__ __launch_bounds__(256) void k_cam_reduce(const float4 *__restrict__ c
       const float hi[9] = {a[9], a[10], a[11], 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
       const float s = wave_sum9_packed(lo);
       const float t = wave_sum9_packed(hi);
-      if (lane < 8) lds[w][j][lane] = s;
-      if (lane == 32) lds[w][j][8] = s;
-      if (lane < 3) lds[w][j][9 + lane] = t;
+      if (mine >= 0) lds[w][j][mine] = s;
+      if (mine >= 0 && mine < 3) lds[w][j][9 + mine] = t;
     }
     __syncthreads();
     for (int e = tid; e < gn * 12; e += 256) {

@@ -1,13 +1,12 @@
 // Tile geometry shared by the forward and backward compositing kernels.
 //
-// The forward walks a tile with a wave per 8 x 8 block (raster_fwd.hip); the
-// backward with one workgroup, or at 16 px with one wave of it: one workgroup per work item, or (a tuning option) persistent
-// workgroups taking items from a work queue.  Records are staged in LDS in
-// batches and read back as broadcasts; per 8 x 8 pixel block a wave visits
-// only the records whose box can reach it (block_masks), so a record that
-// misses a block costs nothing there.  The backward keeps a 16 x 16 block in
-// one wave (four pixels per lane) so the per-record wave reduction is paid
-// once per block (TileCfg below).  Tiles are visited longest list first.
+// Pixels are walked in blocks of 8 x 8, one per lane, mostly a wave per block
+// (the backward's short 16 px lists: four blocks per wave, so the per-record
+// wave reduction is paid once for all four).  A lane tests a record against
+// the block or tile, ballots keep the records that can composite there, and
+// the wave reads those from LDS as broadcasts.  A workgroup takes one work
+// item, or (a tuning option) persistent workgroups take items from a work
+// queue; longest lists come first.
 //
 // Per pixel and Gaussian, with the record's payload (see common.hpp):
 //   dx = (px - i0) - offx,  dy = (py - j0) - offy
@@ -20,13 +19,8 @@
 //
 // The tile lists hold every tile of a record's binning rectangle, but the
 // alpha >= 1/255 ellipse of an elongated or tilted footprint misses many of
-// them.  The backward therefore compacts each batch in LDS to the records
-// that can reach the threshold somewhere in the tile (tile_reaches); the
-// others cost one lane's test instead of box tests and failed alpha
-// evaluations in every pixel slot.  The test is conservative, so the
-// composited sequence of every pixel, and with it every gradient bit, is
-// unchanged.  (In the forward the test's registers cost more occupancy than
-// the skipped records save.)
+// them, and most of a tile's blocks.  The test (tile_reaches) is
+// conservative, so the composited sequence of every pixel is unchanged.
 #pragma once
 
 #include "common.hpp"
@@ -72,99 +66,6 @@ __device__ __forceinline__ bool tile_reaches(const float4 box, const float4 p1, 
   const float big = fmaf(A, um * um, C * (my * my));
   const float thr = __builtin_amdgcn_logf(p2.y) + 0x1.ffa37cp+2f;  // log2(opacity) + log2(255)
   return !(fmin > thr + (0.0625f + 0x1p-18f * big));
-}
-
-// Which staged records each 8 x 8 pixel block of the calling thread's wave
-// can composite.  Every pixel mapping of the compositing kernels gives a wave
-// one 8 x 8 block per pixel slot p, lane l at (l & 7, l >> 3) within it, so
-// the block origin is the pixel of the wave's lane 0.  mk[p][c] bit b: batch
-// record 64 c + b (c < NC, 64 c + b < m) may composite in block p.  Outside
-// the record's compositing box alpha < 1/255 at every pixel centre (the box
-// is the alpha >= 1/255 region's bounding box, with a margin); with ELLIPSE
-// the block must also pass the exact test of tile_reaches (the falloff's
-// minimum over block ∩ box against the threshold, with its rounding margin),
-// which drops the blocks in the corners of a tilted or elongated footprint's
-// box.  Both tests are conservative, so a record whose bit is clear
-// composites nowhere in the block, and within a block the per-pixel alpha
-// test alone decides.  The masks are wave-uniform, so the record loops branch
-// on them in scalar registers and skip records without touching LDS.  Every
-// thread of the group must call this after the batch's payloads are in LDS.
-template <int PPT, int NC, bool ELLIPSE, class Pix>
-__device__ __forceinline__ void block_masks(const float4 *p0, const float4 *p1, const float4 *p2, uint32_t m, int t,
-                                            float ox, float oy, Pix pix, uint64_t (&mk)[PPT][NC]) {
-  float bx[PPT], by[PPT];
-#pragma unroll
-  for (int p = 0; p < PPT; ++p) {
-    int x, y;
-    pix(t & ~(kWave - 1), p, x, y);
-    bx[p] = ox + (float)x;
-    by[p] = oy + (float)y;
-  }
-#pragma unroll
-  for (int c = 0; c < NC; ++c) {
-    const uint32_t j = (uint32_t)(c * kWave + lane_id());
-    const bool live = j < m;
-    const float4 b = p0[live ? j : 0u];
-    if (!ELLIPSE) {
-#pragma unroll
-      for (int p = 0; p < PPT; ++p)
-        mk[p][c] = __ballot(live & (b.x <= bx[p] + 7.0f) & (b.y >= bx[p]) & (b.z <= by[p] + 7.0f) & (b.w >= by[p]));
-    } else {
-      const float4 q1 = p1[live ? j : 0u], q2 = p2[live ? j : 0u];
-#pragma unroll
-      for (int p = 0; p < PPT; ++p) mk[p][c] = __ballot(live && tile_reaches(b, q1, q2, bx[p], by[p], 8.0f));
-    }
-  }
-}
-
-// Slot of this thread's record in the compacted batch: the kept records
-// numbered in thread order.  A workgroup (WG) exchanges its NW per-wave
-// counts through wc with one barrier; a single wave needs none.  Returns the
-// slot (meaningful where keep) and the number kept in `total`.  Every thread
-// of the group must call it.
-template <bool WG, int NW>
-__device__ __forceinline__ uint32_t compact_slot(bool keep, uint32_t *wc, uint32_t &total) {
-  const uint64_t b = __ballot(keep);
-  const uint32_t before = (uint32_t)__popcll(b & lanemask_lt());
-  if (!WG) {
-    total = (uint32_t)__popcll(b);
-    return before;
-  }
-  if (lane_id() == 0) wc[wave_id()] = (uint32_t)__popcll(b);
-  __syncthreads();
-  uint32_t off = 0, tot = 0;
-#pragma unroll
-  for (int w = 0; w < NW; ++w) {
-    const uint32_t c = wc[w];
-    off += w < wave_id() ? c : 0u;
-    tot += c;
-  }
-  total = tot;
-  return off + before;
-}
-
-// Backward: one wave per 16 x 16 block with four pixels per lane, so the
-// 9-value wave reduction of each record is paid once per block.
-template <int TS>
-struct TileCfg {
-  static constexpr int NT = TS == 32 ? 256 : 64;
-  static constexpr int PPT = TS == 8 ? 1 : 4;
-  static constexpr int NW = NT / 64;
-};
-
-template <int TS>
-__device__ __forceinline__ void pixel_of(int t, int p, int &x, int &y) {
-  const int l = t & 63, w = t >> 6;
-  x = l & 7;
-  y = l >> 3;
-  if (TS != 8) {
-    x += (p & 1) * 8;
-    y += (p >> 1) * 8;
-  }
-  if (TS == 32) {
-    x += (w & 1) * 16;
-    y += (w >> 1) * 16;
-  }
 }
 
 // Persistent compositing launches: as many workgroups as the chip holds at

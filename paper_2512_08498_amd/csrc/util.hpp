@@ -97,31 +97,35 @@ __device__ __forceinline__ float pack_add(float a, float b, bool hi) {
   return dpp_add<CTRL>(hi ? b : a, hi ? a : b);
 }
 
-// Wave sums of nine values, with the values packed as the butterfly goes:
-// in-row steps xor 1, xor 2 (quad permutes) and rotate 4 each halve the
-// registers by keeping one value of a pair per lane (9 -> 5 -> 3 -> 2),
-// rotate 8 completes the row sums, and the 32- and 16-lane swaps add the
-// rows.  On return lane l < 8 holds the sum of v[l] and lanes 32..47 the sum
-// of v[8].  Fixed order (deterministic); every lane must be active.
+// Wave sums of nine values, with the values packed as the reduction goes: the
+// 32- and 16-lane swaps fold two values into one register with one add each
+// (9 -> 5 -> 3), rotate 8 and the half-row mirror keep one value of a pair per
+// lane (3 -> 2 -> 1), and the quad permutes complete the sums: 25
+// instructions (33 when the pairwise steps came first, at two selects a pair).
+// On return the sum of v[k] is in lane sum9_lane(k) (and the rest of its
+// quad).  Fixed order (deterministic); every lane must be active.
 __device__ __forceinline__ float wave_sum9_packed(const float (&v)[9]) {
   const int l = lane_id();
-  const bool b0 = l & 1, b1 = (l >> 1) & 1, b2 = (l >> 2) & 1;
-  constexpr int kXor1 = 0xB1, kXor2 = 0x4E, kRor4 = 0x124, kRor8 = 0x128;
-  // xor 1: value 2k + b0 in register k
-  const float p0 = pack_add<kXor1>(v[0], v[1], b0), p1 = pack_add<kXor1>(v[2], v[3], b0);
-  const float p2 = pack_add<kXor1>(v[4], v[5], b0), p3 = pack_add<kXor1>(v[6], v[7], b0);
-  const float p4 = dpp_add<kXor1>(v[8], v[8]);
-  // xor 2: value 4k + 2 b1 + b0 in register k
-  const float q0 = pack_add<kXor2>(p0, p1, b1), q1 = pack_add<kXor2>(p2, p3, b1);
-  const float q2 = dpp_add<kXor2>(p4, p4);
-  // rotate 4: value 4 b2 + 2 b1 + b0 (= l & 7) in r0
-  const float r0 = pack_add<kRor4>(q0, q1, b2);
-  const float r1 = dpp_add<kRor4>(q2, q2);
-  // rotate 8: row sums
-  const float s0 = dpp_add<kRor8>(r0, r0), s1 = dpp_add<kRor8>(r1, r1);
-  // rows: s0 in lanes 0..31, s1 in lanes 32..63, then all four rows
-  const float f = fold32(s0, s1);
-  return fold16(f, f);
+  const bool b2 = (l >> 2) & 1, b3 = (l >> 3) & 1;
+  constexpr int kXor1 = 0xB1, kXor2 = 0x4E, kRor8 = 0x128, kHalfMirror = 0x141;
+  const float a = fold32(v[0], v[1]), b = fold32(v[2], v[3]);
+  const float c = fold32(v[4], v[5]), d = fold32(v[6], v[7]), e = fold32(v[8], v[8]);
+  // rows of 16 lanes: x = (v0, v2, v1, v3), y = (v4, v6, v5, v7), z = v8
+  const float x = fold16(a, b), y = fold16(c, d), z = fold16(e, e);
+  const float t = pack_add<kRor8>(x, y, b3);       // x in lanes 0..7 of a row, y in 8..15
+  const float r = pack_add<kHalfMirror>(t, dpp_add<kRor8>(z, z), b2);  // z in lanes with bit 2
+  const float s = dpp_add<kXor1>(r, r);
+  return dpp_add<kXor2>(s, s);
+}
+
+// First lane holding the sum of v[k] after wave_sum9_packed, and its inverse:
+// the value whose sum this lane is to write, or -1.
+__device__ __forceinline__ constexpr int sum9_lane(int k) {
+  return k == 8 ? 4 : ((k & 1) << 5) | ((k & 2) << 3) | ((k & 4) << 1);
+}
+__device__ __forceinline__ int sum9_value(int lane) {
+  if (lane == 4) return 8;
+  return (lane & 7) ? -1 : (lane >> 5) | ((lane >> 3) & 2) | ((lane >> 1) & 4);
 }
 
 

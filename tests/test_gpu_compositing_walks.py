@@ -1,7 +1,8 @@
 """The compositing walks that a launch's size chooses between give the same
 results: the forward's groups of two and four records bit for bit, on lists
 that end at every remainder of a group and a 64-entry step, with pixels that
-stop in them and tiles cut by the image's edge."""
+stop in them and tiles cut by the image's edge; the backward's walks up to the
+order of their sums."""
 import numpy as np
 import pytest
 import torch
@@ -45,3 +46,45 @@ def test_forward_groups_agree_bitwise(ts, n, opacity_mean):
     if n == 3000:
         assert int((a["t_final"] < 2e-4).sum()) > 50  # pixels that stopped
     log(f"ts {ts}, {n} Gaussians: longest walk {int(a['last_pos'].max())}, {int(a['n_contrib'].max())} composited")
+
+
+def _grads(sc, params, cam, ts, long_list, spoil):
+    rast = Rasterizer([cam], sc.n, sc.sh_degree, tile_size=ts, long_list=long_list, capacity_records=max(sc.n, 1),
+                      capacity_pairs=max(200 * sc.n, 1))
+    out = rast.forward(params)
+    rng = np.random.default_rng(9)
+    dl = rng.uniform(-1.0, 1.0, (3, cam.height, cam.width)).astype(np.float32)
+    if spoil:  # one pixel's gradient is not finite
+        dl[:, cam.height // 2, cam.width // 4] = (np.nan, np.inf, -np.inf)
+    g = rast.backward(params, out, torch.from_numpy(dl.reshape(-1)).cuda())
+    return {k: v.double().cpu().numpy() for k, v in g.items() if v is not None}
+
+
+@pytest.mark.parametrize("w, h, n, spoil", [(133, 101, 0, False), (133, 101, 1, False), (133, 101, 65, False),
+                                            (133, 101, 3000, False), (133, 101, 3000, True),
+                                            (1293, 1021, 120_000, False), (1293, 1021, 120_000, True)])
+def test_backward_walks_agree(w, h, n, spoil):
+    """A wave per 16 px tile (every list under 32 entries; at 1293 x 1021
+    nearly all lists, as none holds a 4096th of the pairs) and a wave per 8 x 8
+    block (long_list 0, and the other tile sizes) form the same terms per
+    pixel and add them in another order: up to 24 additions of 2^-24 each,
+    1.4e-6 of the absolute terms, seven times that for their cancellation.  A
+    pixel whose gradient is not finite reaches the Gaussians it composited and
+    no others, in every walk."""
+    f = 120.0 * w / 133
+    cam = camera(f, w, h)
+    sc = _stack(n, 11 + n, 2.0, w, h, f)
+    if n > 3000:
+        sc.log_scale[:] -= 1.2
+    params = device_params(sc)
+    ref = _grads(sc, params, cam, 16, 1024, spoil)
+    for ts, long_list in ((16, 0), (16, 5), (8, 1024), (32, 1024)):
+        got = _grads(sc, params, cam, ts, long_list, spoil)
+        for k, a in ref.items():
+            fin = np.isfinite(a)
+            assert np.array_equal(fin, np.isfinite(got[k])), (ts, long_list, k)
+            if n > 1:
+                assert fin.all() != spoil, k
+            d = np.linalg.norm(got[k][fin] - a[fin]) / max(np.linalg.norm(a[fin]), 1e-30)
+            assert d <= 1e-5, (ts, long_list, k, d)
+    log(f"{w}x{h}, {n} Gaussians, spoil {spoil}: " + ", ".join(f"{k} {int(np.isfinite(v).sum())}" for k, v in ref.items()))
