@@ -4,25 +4,31 @@
 // of arbitrary sizes; the n x n box downsampling of the LOD levels; and the
 // per-frame ratios, level updates and ratio-weighted frame draws.
 //
-// X takes two passes over HBM.  Row pass: one workgroup per image row packs
-// the red and green rows into one complex FFT (z = R + iG; R and G are
-// separated by the Hermitian symmetry of real inputs) and the blue row into a
-// second, and writes the half spectrum j = 0..W/2 of each channel transposed
-// (column-major per channel), so the column pass reads contiguous columns.
-// Consecutive rows run on one XCD, so the transposed 8-byte writes of
-// neighbouring rows meet in the same L2.  Column pass: one workgroup per
-// half-spectrum column FFTs the three channels' columns, adds |F|^2 over the
-// channels per bin, and sums the square roots; columns 1..ceil(W/2)-1 count
-// twice (their mirror W - j has the same magnitudes).  A last pass sums each
-// image's columns in order.
+// X takes two passes over HBM.  Row pass: a workgroup packs two rows of a
+// channel into one complex FFT (z = row i + i row i+1; the two are separated
+// by the Hermitian symmetry of real inputs), three channels and one or more
+// such pairs at once, and writes the half spectrum j = 0..W/2 of each channel
+// transposed (column-major per channel, the pair's two values side by side),
+// so the column pass reads contiguous columns.  Neighbouring pairs run on one
+// XCD, so their transposed 16-byte writes meet in the same L2.  Column pass: a
+// workgroup FFTs the three channels of one or more half-spectrum columns, adds
+// |F|^2 over the channels per bin, and sums the square roots; columns
+// 1..ceil(W/2)-1 count twice (their mirror W - j has the same magnitudes).  A
+// last pass sums each image's columns in order.
 //
 // The FFT is Stockham's self-sorting mixed-radix form (radices 2, 3, 4, 5,
-// 7 and the composites 8, 9, 15, 16, 20, 25, 27, planned for the fewest
-// stages), one stage per radix over all sequences of the workgroup at once
-// (the two packed rows, or the three channels' columns), in one LDS buffer:
-// every thread loads and transforms its butterflies in registers, then
-// stores them after a barrier.  The twiddles exp(-2 pi i t / N) come from a
-// table per transform length computed in double precision at plan time.
+// 7 and the composites 6, 8, 9, 10, 12, 15, 16; see fft_plan), one stage per
+// radix over all sequences of the workgroup at once, in one LDS buffer: the
+// first stage's butterflies are loaded from global memory, and the column
+// pass's last stage keeps its bins in registers.  The twiddles come from a
+// table per transform length computed in double precision at plan time, in
+// the order in which the stages read them.
+//
+// What bounds the two passes is the LDS and the stages' latency, not HBM (the
+// six 1600x900 views of a rig: 104 MB in, 104 MB out and in again).  They
+// take 64 and 43 us there; with the blue row alone in its transform, a copy of
+// the row and of the twiddles through LDS and the buffer behind generic
+// pointers (flat instructions, 151 and 211 VGPRs) it was 115 and 119.
 #include <cfloat>
 
 #include "kernels.hpp"
@@ -90,13 +96,13 @@ template <int P>
 struct Split {
   static constexpr int A = 1, B = P;
 };
+template <> struct Split<6> { static constexpr int A = 2, B = 3; };
 template <> struct Split<8> { static constexpr int A = 4, B = 2; };
 template <> struct Split<9> { static constexpr int A = 3, B = 3; };
+template <> struct Split<10> { static constexpr int A = 2, B = 5; };
+template <> struct Split<12> { static constexpr int A = 4, B = 3; };
 template <> struct Split<15> { static constexpr int A = 3, B = 5; };
 template <> struct Split<16> { static constexpr int A = 4, B = 4; };
-template <> struct Split<20> { static constexpr int A = 4, B = 5; };
-template <> struct Split<25> { static constexpr int A = 5, B = 5; };
-template <> struct Split<27> { static constexpr int A = 3, B = 9; };
 
 // cos and sin at compile time: Taylor series in double on |x| <= pi (30
 // terms, far below float resolution).
@@ -161,12 +167,13 @@ __device__ __forceinline__ void dft_composite(float2 *v) {
     for (int b = 0; b < B; ++b) v[a + A * b] = t[a * B + b];
 }
 
-// In-register radix-P DFT with the forward sign.  Radices 3 and 5 use the
+// In-register radix-P DFT with the forward sign (P = 1: nothing).  Radices 3 and 5 use the
 // symmetric forms: with s_k = x_k + x_{P-k} and d_k = x_k - x_{P-k},
 // X_q = x_0 + sum_k cos(2 pi k q / P) s_k - i sum_k sin(2 pi k q / P) d_k.
 template <int P>
 __device__ __forceinline__ void dft(float2 *v) {
-  if constexpr (Split<P>::A > 1) {
+  if constexpr (P == 1) {
+  } else if constexpr (Split<P>::A > 1) {
     dft_composite<P>(v);
   } else if constexpr (P == 3) {
     constexpr float s1 = 0.86602540378443865f;  // sin(2 pi / 3)
@@ -218,46 +225,90 @@ __device__ __forceinline__ void dft(float2 *v) {
   }
 }
 
-constexpr int kRowThreads = 256;                // row pass: two sequences of length W
-constexpr int kColThreads = 256;                // column pass: three sequences of length H
-constexpr int kRowMaxElems = 2 * 2560;
-constexpr int kColMaxElems = 3 * 2560;
 
-// One radix-P Stockham stage over `cnt` sequences of length N stored one
-// after the other in buf.  Butterfly b (sequence b / m, index j = b mod m,
-// m = N / P) reads elements j + r m, multiplies by the twiddles
-// exp(-2 pi i k r / (Ns P)) (k = j mod Ns; table entry k r N / (Ns P)),
-// transforms, and writes (j / Ns) Ns P + k + q Ns.  All butterflies of the
-// thread are loaded and transformed before the barrier, then stored, so one
-// LDS buffer suffices.  Not inlined: each radix then gets its own register
-// allocation (71 to 113 VGPRs), where inlining all five into the stage loop
-// made the kernels allocate for their union (241 VGPRs, two waves per SIMD
-// instead of three).
+// The workgroup's buffer: an LDS pointer of its own kind, so that the stages,
+// which are calls, take ds_ instructions.
+typedef float v2f __attribute__((ext_vector_type(2)));
+typedef __attribute__((address_space(3))) v2f Lds2;
+
+__device__ __forceinline__ float2 get(const Lds2 *p) {
+  const v2f t = *p;
+  return make_float2(t.x, t.y);
+}
+__device__ __forceinline__ void put(Lds2 *p, float2 x) {
+  v2f t;
+  t.x = x.x;
+  t.y = x.y;
+  *p = t;
+}
+
+// A radix-P Stockham stage over `cnt` sequences of length N stored one after
+// the other.  Butterfly b (sequence b / m, index j = b mod m, m = N / P)
+// reads elements j + r m, multiplies by the twiddles exp(-2 pi i k r / (Ns P))
+// (k = j mod Ns; table entry (r - 1) Ns + k of the stage), transforms, and
+// writes (j / Ns) Ns P + k + q Ns.  The stages are not inlined: each radix
+// then gets its own register allocation.
+
+// First stage (Ns = 1, no twiddles) of the row pass: sequence 3 p + c packs
+// rows row0 + 2 p and the next of channel c (zeros past the last row).
+template <int P, int T>
+__device__ __forceinline__ void rows_in(Lds2 *buf, const float *img, int W, int H, int row0, int cnt) {
+  const int m = W / P, total = cnt * m;
+  const float inv_m = 1.0f / (float)m;
+  for (int b = threadIdx.x; b < total; b += T) {
+    const int seq = fdiv(b, m, inv_m), j = b - seq * m, pair = seq / 3, c = seq - 3 * pair;
+    const int row = row0 + 2 * pair;
+    const float *src = img + ((int64_t)c * H + row) * W + j;
+    const bool two = row + 1 < H;
+    float2 v[P];
+#pragma unroll
+    for (int r = 0; r < P; ++r) v[r] = make_float2(src[r * m], two ? src[W + r * m] : 0.0f);
+    dft<P>(v);
+#pragma unroll
+    for (int q = 0; q < P; ++q) put(buf + seq * W + j * P + q, v[q]);
+  }
+}
+
+// First stage of the column pass: sequence 3 k + c is column col0 + k of
+// channel c.
+template <int P, int T>
+__device__ __forceinline__ void cols_in(Lds2 *buf, const float2 *inter, int H, int pitch, int half, int col0,
+                                                  int cnt) {
+  const int m = H / P, total = cnt * m;
+  const float inv_m = 1.0f / (float)m;
+  for (int b = threadIdx.x; b < total; b += T) {
+    const int seq = fdiv(b, m, inv_m), j = b - seq * m, k = seq / 3, c = seq - 3 * k;
+    const float2 *src = inter + ((int64_t)c * half + col0 + k) * pitch + j;
+    float2 v[P];
+#pragma unroll
+    for (int r = 0; r < P; ++r) v[r] = src[r * m];
+    dft<P>(v);
+#pragma unroll
+    for (int q = 0; q < P; ++q) put(buf + seq * H + j * P + q, v[q]);
+  }
+}
+
+// A later stage in LDS.  All butterflies of the thread are loaded and
+// transformed before the barrier, then stored, so one buffer suffices.
 template <int P, int T, int MAXE>
-__device__ __attribute__((noinline)) void fft_stage(float2 *buf, int N, int cnt, int Ns, const float2 *tw) {
+__device__ __forceinline__ void stage(Lds2 *buf, int N, int cnt, int Ns, const float2 *tw) {
+  int t0 = threadIdx.x;
+  asm volatile("" : "+v"(t0));  // keeps every radix's indices from being computed ahead of the loop over the stages
   constexpr int kMaxB = (MAXE / P + T - 1) / T;
-  const int m = N / P;
-  const int total = cnt * m;
-  const int tstep = N / (Ns * P);
-  const float inv_ns = 1.0f / (float)Ns;
-  const bool first = Ns == 1;  // k = 0: no twiddles, no division
+  const int m = N / P, total = cnt * m;
+  const float inv_m = 1.0f / (float)m, inv_ns = 1.0f / (float)Ns;
   float2 v[kMaxB][P];
   int dst[kMaxB];
 #pragma unroll
   for (int i = 0; i < kMaxB; ++i) {
-    const int b = threadIdx.x + i * T;
+    const int b = t0 + i * T;
     if (b < total) {
-      const int seq = (b >= m ? 1 : 0) + (b >= 2 * m ? 1 : 0);  // cnt <= 3
-      const int j = b - seq * m;
-      const int jq = first ? j : fdiv(j, Ns, inv_ns);
-      const int k = j - jq * Ns;
-      const float2 *src = buf + seq * N + j;
+      const int seq = fdiv(b, m, inv_m), j = b - seq * m;
+      const int jq = fdiv(j, Ns, inv_ns), k = j - jq * Ns;
+      const Lds2 *src = buf + seq * N + j;
+      v[i][0] = get(src);
 #pragma unroll
-      for (int r = 0; r < P; ++r) v[i][r] = src[r * m];
-      if (!first) {
-#pragma unroll
-        for (int r = 1; r < P; ++r) v[i][r] = cmul(v[i][r], tw[k * r * tstep]);
-      }
+      for (int r = 1; r < P; ++r) v[i][r] = cmul(get(src + r * m), tw[(r - 1) * Ns + k]);
       dft<P>(v[i]);
       dst[i] = seq * N + jq * Ns * P + k;
     }
@@ -265,46 +316,97 @@ __device__ __attribute__((noinline)) void fft_stage(float2 *buf, int N, int cnt,
   __syncthreads();
 #pragma unroll
   for (int i = 0; i < kMaxB; ++i) {
-    const int b = threadIdx.x + i * T;
+    const int b = t0 + i * T;
     if (b < total) {
 #pragma unroll
-      for (int q = 0; q < P; ++q) buf[dst[i] + q * Ns] = v[i][q];
+      for (int q = 0; q < P; ++q) put(buf + dst[i] + q * Ns, v[i][q]);
     }
   }
-  __syncthreads();
 }
 
-// Forward DFTs, in place, of cnt sequences of length N in LDS (cnt * N <=
-// MAXE) by a workgroup of T threads; tw is the length-N table
-// exp(-2 pi i t / N), also in LDS.  Every thread must call it.
-template <int T, int MAXE>
-__device__ __forceinline__ void fft_lds(float2 *buf, int N, int cnt, const float2 *tw, const uint8_t *__restrict__ fac,
-                                        int nfac) {
-  int Ns = 1;
-  for (int s = 0; s < nfac; ++s) {
-    switch (fac[s]) {
-      case 27: fft_stage<27, T, MAXE>(buf, N, cnt, Ns, tw); break;
-      case 25: fft_stage<25, T, MAXE>(buf, N, cnt, Ns, tw); break;
-      case 20: fft_stage<20, T, MAXE>(buf, N, cnt, Ns, tw); break;
-      case 16: fft_stage<16, T, MAXE>(buf, N, cnt, Ns, tw); break;
-      case 15: fft_stage<15, T, MAXE>(buf, N, cnt, Ns, tw); break;
-      case 9: fft_stage<9, T, MAXE>(buf, N, cnt, Ns, tw); break;
-      case 8: fft_stage<8, T, MAXE>(buf, N, cnt, Ns, tw); break;
-      case 4: fft_stage<4, T, MAXE>(buf, N, cnt, Ns, tw); break;
-      case 2: fft_stage<2, T, MAXE>(buf, N, cnt, Ns, tw); break;
-      case 3: fft_stage<3, T, MAXE>(buf, N, cnt, Ns, tw); break;
-      case 5: fft_stage<5, T, MAXE>(buf, N, cnt, Ns, tw); break;
-      default: fft_stage<7, T, MAXE>(buf, N, cnt, Ns, tw); break;
+// Last stage (Ns = m) of the column pass: butterfly b of `cols` columns takes
+// the three channels in turn and leaves the sum of its bins' norms in part[b].
+template <int P, int T>
+__device__ __forceinline__ void cols_out(const Lds2 *buf, int H, int cols, const float2 *tw,
+                                                   __attribute__((address_space(3))) float *part) {
+  const int m = H / P, total = cols * m;
+  const float inv_m = 1.0f / (float)m;
+  for (int b = threadIdx.x; b < total; b += T) {
+    const int k = fdiv(b, m, inv_m), j = b - k * m;
+    const Lds2 *src = buf + 3 * k * H + j;
+    float2 w[P];
+#pragma unroll
+    for (int r = 1; r < P; ++r) w[r] = tw[(r - 1) * m + j];
+    float acc[P];
+#pragma unroll
+    for (int q = 0; q < P; ++q) acc[q] = 0.0f;
+#pragma unroll 1
+    for (int c = 0; c < 3; ++c) {
+      float2 v[P];
+      v[0] = get(src + c * H);
+#pragma unroll
+      for (int r = 1; r < P; ++r) v[r] = cmul(get(src + c * H + r * m), w[r]);
+      dft<P>(v);
+#pragma unroll
+      for (int q = 0; q < P; ++q) acc[q] += v[q].x * v[q].x + v[q].y * v[q].y;
     }
+    float s = 0.0f;
+#pragma unroll
+    for (int q = 0; q < P; ++q) s += sqrtf(acc[q]);
+    part[b] = s;
+  }
+}
+
+template <int P>
+struct Radix {
+  static constexpr int value = P;
+};
+
+// Calls f with the radix as a compile-time constant.
+template <bool SMALL, class F>
+__device__ __forceinline__ void with_radix(int p, const F &f) {
+  switch (p) {
+    case 16: f(Radix<16>()); break;
+    case 15: f(Radix<15>()); break;
+    case 12: f(Radix<12>()); break;
+    case 10: f(Radix<10>()); break;
+    case 9: f(Radix<9>()); break;
+    case 8: f(Radix<8>()); break;
+    case 7: f(Radix<7>()); break;
+    case 6: f(Radix<6>()); break;
+    case 5: f(Radix<5>()); break;
+    default:
+      if constexpr (SMALL) {
+        if (p == 4) f(Radix<4>());
+        else if (p == 3) f(Radix<3>());
+        else if (p == 2) f(Radix<2>());
+        else f(Radix<1>());
+      }
+  }
+}
+
+// The stages fac[1 .. last) between a first one and, for the column pass, a
+// last one.  Returns Ns behind them.  A stage's table follows those of the
+// stages before, whose sizes add up to Ns - fac[0].
+template <int T, int MAXE>
+__device__ __forceinline__ int middle_stages(Lds2 *buf, int N, int cnt, const uint8_t *__restrict__ fac, int last,
+                                             const float2 *__restrict__ tw) {
+  int Ns = fac[0];
+  __syncthreads();
+  for (int s = 1; s < last; ++s) {
+    const float2 *t = tw + (Ns - fac[0]);
+    with_radix<false>(fac[s], [&](auto p) { stage<decltype(p)::value, T, MAXE>(buf, N, cnt, Ns, t); });
+    __syncthreads();
     Ns *= fac[s];
   }
+  return Ns;
 }
 
 __device__ __forceinline__ int find_image(const FreqImg *imgs, int n, int64_t idx, bool rows) {
   int lo = 0, hi = n - 1;
   while (lo < hi) {
     const int mid = (lo + hi + 1) >> 1;
-    if ((rows ? imgs[mid].row_base : imgs[mid].col_base) <= idx) lo = mid;
+    if ((rows ? imgs[mid].row_group : imgs[mid].col_group) <= idx) lo = mid;
     else hi = mid - 1;
   }
   return lo;
@@ -324,71 +426,66 @@ __device__ __forceinline__ float block_sum(float x, float *red) {
   return t;
 }
 
-__global__ __launch_bounds__(kRowThreads) void k_fft_rows(const float *__restrict__ images, const FreqImg *__restrict__ imgs,
-                                                  int n_imgs, int64_t n_rows, const float2 *__restrict__ tw_all,
-                                                  float2 *__restrict__ inter) {
+__global__ __launch_bounds__(kFreqRowThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_fft_rows(
+    const float *__restrict__ images, const FreqImg *__restrict__ imgs, int n_imgs, int64_t n_groups,
+    const float2 *__restrict__ tw_all, float2 *__restrict__ inter) {
+  constexpr int T = kFreqRowThreads;
   extern __shared__ float2 lds[];
-  const int64_t row = xcd_tile(blockIdx.x, gridDim.x);
-  if (row >= n_rows) return;
-  const FreqImg *ip = imgs + find_image(imgs, n_imgs, row, true);
+  Lds2 *buf = (Lds2 *)lds;
+  const int64_t group = xcd_tile(blockIdx.x, gridDim.x);
+  if (group >= n_groups) return;
+  const FreqImg *ip = imgs + find_image(imgs, n_imgs, group, true);
   const FreqImg im = *ip;
-  const int i = (int)(row - im.row_base), W = im.w, H = im.h, half = W / 2 + 1;
-  const float *R = images + im.pix_off + (int64_t)i * W;
-  const float *G = R + (int64_t)W * H, *B = G + (int64_t)W * H;
-  // sequence 0: R + iG, sequence 1: B; then the twiddle table
-  float2 *tw = lds + 2 * W;
-  const float2 *twg = tw_all + im.tw_w;
-  for (int x = threadIdx.x; x < W; x += blockDim.x) {
-    lds[x] = make_float2(R[x], G[x]);
-    lds[W + x] = make_float2(B[x], 0.0f);
-    tw[x] = twg[x];
-  }
-  __syncthreads();
-  fft_lds<kRowThreads, kRowMaxElems>(lds, W, 2, tw, ip->fac_w, im.nfac_w);
+  const int W = im.w, H = im.h, half = W / 2 + 1, pitch = freq_pitch(H);
+  const int row0 = (int)(group - im.row_group) * 2 * im.pairs;
+  const int pairs = min(im.pairs, (H - row0 + 1) / 2), cnt = 3 * pairs;
+  with_radix<true>(ip->fac_w[0], [&](auto p) { rows_in<decltype(p)::value, T>(buf, images + im.pix_off, W, H, row0, cnt); });
+  middle_stages<T, kFreqRowElems>(buf, W, cnt, ip->fac_w, im.nfac_w, tw_all + im.tw_w);
   float2 *out = inter + im.inter_off;
-  for (int j = threadIdx.x; j < half; j += blockDim.x) {
-    const float2 p = lds[j], q = lds[j == 0 ? 0 : W - j];
-    // F_R = (Z(j) + conj Z(-j)) / 2,  F_G = (Z(j) - conj Z(-j)) / 2i
-    out[((int64_t)0 * half + j) * H + i] = make_float2(0.5f * (p.x + q.x), 0.5f * (p.y - q.y));
-    out[((int64_t)1 * half + j) * H + i] = make_float2(0.5f * (p.y + q.y), -0.5f * (p.x - q.x));
-    out[((int64_t)2 * half + j) * H + i] = lds[W + j];
-  }
+  const int total = half * pairs;
+  const float inv_p = 1.0f / (float)pairs;
+  for (int c = 0; c < 3; ++c)
+    for (int b = threadIdx.x; b < total; b += T) {
+      const int j = pairs == 1 ? b : fdiv(b, pairs, inv_p), pair = b - j * pairs;
+      const Lds2 *z = buf + (3 * pair + c) * W;
+      const float2 p = get(z + j), q = get(z + (j == 0 ? 0 : W - j));
+      // F_i = (Z(j) + conj Z(-j)) / 2,  F_i+1 = (Z(j) - conj Z(-j)) / 2i
+      *reinterpret_cast<float4 *>(out + ((int64_t)c * half + j) * pitch + row0 + 2 * pair) =
+          make_float4(0.5f * (p.x + q.x), 0.5f * (p.y - q.y), 0.5f * (p.y + q.y), -0.5f * (p.x - q.x));
+    }
 }
 
-constexpr int kMaxBinsPerThread = (2560 + kColThreads - 1) / kColThreads;  // H <= 2560
-
-__global__ __launch_bounds__(kColThreads) void k_fft_cols(const FreqImg *__restrict__ imgs, int n_imgs, int64_t n_cols,
-                                                  const float2 *__restrict__ tw_all,
-                                                  const float2 *__restrict__ inter, float *__restrict__ col_sum) {
+__global__ __launch_bounds__(kFreqColThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_fft_cols(
+    const FreqImg *__restrict__ imgs, int n_imgs, int64_t n_groups, const float2 *__restrict__ tw_all,
+    const float2 *__restrict__ inter, float *__restrict__ col_sum) {
+  constexpr int T = kFreqColThreads;
   extern __shared__ float2 lds[];
-  __shared__ float red[kColThreads / 64];
-  const int64_t col = blockIdx.x;
-  if (col >= n_cols) return;
-  const FreqImg *ip = imgs + find_image(imgs, n_imgs, col, false);
+  Lds2 *buf = (Lds2 *)lds;
+  const int64_t group = blockIdx.x;
+  if (group >= n_groups) return;
+  const FreqImg *ip = imgs + find_image(imgs, n_imgs, group, false);
   const FreqImg im = *ip;
-  const int j = (int)(col - im.col_base), W = im.w, H = im.h, half = W / 2 + 1;
-  float2 *tw = lds + 3 * H;
-  const float2 *twg = tw_all + im.tw_h;
-  for (int k = threadIdx.x; k < H; k += blockDim.x) tw[k] = twg[k];
-  for (int c = 0; c < 3; ++c) {
-    const float2 *src = inter + im.inter_off + ((int64_t)c * half + j) * H;
-    for (int k = threadIdx.x; k < H; k += blockDim.x) lds[c * H + k] = src[k];
-  }
+  const int W = im.w, H = im.h, half = W / 2 + 1;
+  const int col0 = (int)(group - im.col_group) * im.cols, cols = min(im.cols, half - col0), cnt = 3 * cols;
+  with_radix<true>(ip->fac_h[0], [&](auto p) {
+    cols_in<decltype(p)::value, T>(buf, inter + im.inter_off, H, freq_pitch(H), half, col0, cnt);
+  });
+  const float2 *tw = tw_all + im.tw_h;
+  const int Ns = middle_stages<T, 3 * kFreqMaxN>(buf, H, cnt, ip->fac_h, im.nfac_h - 1, tw);
+  auto *part = (__attribute__((address_space(3))) float *)(buf + cnt * H);
+  with_radix<true>(ip->fac_h[im.nfac_h - 1],
+             [&](auto p) { cols_out<decltype(p)::value, T>(buf, H, cols, tw + (Ns - ip->fac_h[0]), part); });
   __syncthreads();
-  fft_lds<kColThreads, kColMaxElems>(lds, H, 3, tw, ip->fac_h, im.nfac_h);
-  float s = 0.0f;
+  // a wave per column: lane l adds values l, l + 64, ..., then the lanes
+  const int lane = threadIdx.x & 63;
+  for (int k = threadIdx.x >> 6; k < cols; k += T / 64) {
+    float s = 0.0f;
+    for (int i = lane; i < Ns; i += 64) s += part[k * Ns + i];
 #pragma unroll
-  for (int t = 0; t < kMaxBinsPerThread; ++t) {
-    const int k = threadIdx.x + t * kColThreads;
-    if (k < H) {
-      const float2 a = lds[k], b = lds[H + k], c = lds[2 * H + k];
-      s += sqrtf((a.x * a.x + a.y * a.y) + (b.x * b.x + b.y * b.y) + (c.x * c.x + c.y * c.y));
-    }
-  }
-  const float total = block_sum<kColThreads / 64>(s, red);
-  if (threadIdx.x == 0) {
+    for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off);
+    const int j = col0 + k;
     const bool single = j == 0 || (W % 2 == 0 && j == W / 2);
-    col_sum[col] = single ? total : 2.0f * total;
+    if (lane == 0) col_sum[im.col_base + j] = single ? s : 2.0f * s;
   }
 }
 
@@ -476,14 +573,13 @@ __global__ __launch_bounds__(256) void k_freq_schedule(const float *__restrict__
 
 }  // namespace
 
-void launch_freq_significance(const float *images, const FreqImg *imgs, int n_imgs, int64_t n_rows, int64_t n_cols,
-                              int max_w, int max_h, const float2 *tw, float2 *inter, float *col_sum, float *X,
-                              hipStream_t st) {
+void launch_freq_significance(const float *images, const FreqImg *imgs, int n_imgs, int64_t row_groups,
+                              int64_t col_groups, uint32_t lds_rows, uint32_t lds_cols, const float2 *tw, float2 *inter,
+                              float *col_sum, float *X, hipStream_t st) {
   if (n_imgs == 0) return;
-  const uint32_t grid = tile_grid((uint32_t)n_rows);
-  k_fft_rows<<<grid, kRowThreads, (size_t)3 * max_w * sizeof(float2), st>>>(images, imgs, n_imgs, n_rows, tw, inter);
-  k_fft_cols<<<(unsigned)n_cols, kColThreads, (size_t)4 * max_h * sizeof(float2), st>>>(imgs, n_imgs, n_cols, tw,
-                                                                                        inter, col_sum);
+  const uint32_t grid = tile_grid((uint32_t)row_groups);
+  k_fft_rows<<<grid, kFreqRowThreads, lds_rows, st>>>(images, imgs, n_imgs, row_groups, tw, inter);
+  k_fft_cols<<<(unsigned)col_groups, kFreqColThreads, lds_cols, st>>>(imgs, n_imgs, col_groups, tw, inter, col_sum);
   k_freq_final<<<(unsigned)n_imgs, 256, 0, st>>>(imgs, col_sum, X);
 }
 

@@ -24,15 +24,31 @@ struct RigIdx {
 
 // One image of a frequency-significance batch: planar RGB [3][h][w] at float
 // offset pix_off; its half spectrum (w/2 + 1 columns of h bins per channel,
-// column-major) at float2 offset inter_off; its rows and half-spectrum
-// columns numbered from row_base and col_base across the batch.  fac_* are
-// the radices of the row (w) and column (h) transforms, tw_* the offsets of
-// their twiddle tables exp(-2 pi i t / n), t < n, in the batch's table.
+// column-major, freq_pitch(h) apart) at float2 offset inter_off; its
+// half-spectrum columns numbered from col_base across the batch.  A workgroup
+// takes `pairs` pairs of rows, or `cols` columns; the workgroups of the two
+// passes are numbered from row_group and col_group.  fac_* are the radices of
+// the row (w) and column (h) transforms, tw_* the offsets of their twiddles
+// in the batch's table: per stage after the first, exp(-2 pi i k r / (Ns P))
+// at (r - 1) Ns + k for its radix P, Ns the product of the radices before.
 struct FreqImg {
-  int32_t w, h, nfac_w, nfac_h;
+  int32_t w, h, nfac_w, nfac_h, pairs, cols;
   uint8_t fac_w[16], fac_h[16];
-  int64_t pix_off, inter_off, row_base, col_base, tw_w, tw_h;
+  int64_t pix_off, inter_off, col_base, row_group, col_group, tw_w, tw_h;
 };
+
+constexpr int kFreqMaxN = 2560;     // longest row or column transform
+// The two passes' workgroups, the values they take (three sequences at
+// least) and the workgroups that a batch should leave.  The row pass takes as
+// much as LDS allows, as a workgroup's rows are the bytes it writes side by
+// side: the rig's six 1600x900 views 64 us with two pairs, 73 with one, and
+// four mixed ones and their halves 55 us (74).  The column pass takes as
+// little as fills its threads: 43 us and 36, with 512 threads 44 and 40, with
+// 128 58 and 52.
+constexpr int kFreqRowThreads = 512, kFreqColThreads = 256;
+constexpr int kFreqRowElems = 9728, kFreqColElems = 3072;
+constexpr int kFreqRowGroups = 128, kFreqColGroups = 256;
+__host__ __device__ constexpr int freq_pitch(int h) { return (h + 1) & ~1; }
 
 // Taps of the sampled LoG: g (Gaussian, sum 1) and h (second derivative,
 // sum 0, second moment 2) at offsets -R..R, R <= 5 (room for R <= 8).
@@ -81,9 +97,9 @@ void launch_reduce_pairs(const Ws &ws, const Sizes &sz, int32_t *step, hipStream
 void launch_pre_bwd(const GaussPtrs &gp, const Cam *cams, const Ws &ws, const Sizes &sz, int sh_degree,
                     const MutPtrs *grads, int accumulate, const AdamArgs *adam, float4 *cam_rec, hipStream_t st);
 uint32_t cam_chunks(uint32_t cap_rec);
-void launch_freq_significance(const float *images, const FreqImg *imgs, int n_imgs, int64_t n_rows, int64_t n_cols,
-                              int max_w, int max_h, const float2 *tw, float2 *inter, float *col_sum, float *X,
-                              hipStream_t st);
+void launch_freq_significance(const float *images, const FreqImg *imgs, int n_imgs, int64_t row_groups,
+                              int64_t col_groups, uint32_t lds_rows, uint32_t lds_cols, const float2 *tw, float2 *inter,
+                              float *col_sum, float *X, hipStream_t st);
 uint32_t ins_tiles(const ViewInfo *views_host, int n_views);
 uint32_t ins_blocks(int64_t n_pix);
 size_t ins_lds_bytes(int R);

@@ -51,8 +51,8 @@ struct gsr_ctx {
   std::vector<FreqImg> freq;
   FreqImg *freq_d = nullptr;
   float2 *freq_tw_d = nullptr;
-  int64_t freq_rows = 0, freq_cols = 0, freq_inter = 0;
-  int32_t freq_max_w = 0, freq_max_h = 0;
+  int64_t freq_row_groups = 0, freq_col_groups = 0, freq_inter = 0;
+  uint32_t freq_lds_rows = 0, freq_lds_cols = 0;
   size_t freq_ws = 0;
   // tuning applied at the next gsr_plan
   int32_t tuned_ts = 16;
@@ -219,30 +219,87 @@ int64_t total_px(const gsr_ctx *c) {
 
 float *cam_part(const gsr_ctx *c, void *base) { return reinterpret_cast<float *>(static_cast<char *>(base) + c->lay.cam_part); }
 
-// Stage radices of an FFT of length n: the fewest stages over the radices
-// the kernels implement (composites 27, 25, 20, 16, 15, 9, 8 and primes 7,
-// 5, 3, 2; ties to the larger first radix); false if n has a prime factor
-// above 7 or needs more than 16 stages.
-bool fft_radices(int n, uint8_t *fac, int32_t &nfac) {
-  static const int kRadices[] = {27, 25, 20, 16, 15, 9, 8, 7, 5, 4, 3, 2};
+// Stage radices of an FFT of `cnt` sequences of length n (see freq.hip) over
+// the radices the kernels implement; false if n has a prime factor above 7.
+// They are chosen for the least time, counted as the rounds in which the
+// workgroup's threads take a stage's butterflies times a butterfly's
+// instructions (its transform, 8 per value for the LDS and the twiddles, 20
+// for its indices), and 150 per stage for the barriers.  A first stage of even
+// radix writes to few LDS banks, so an odd one goes first where there is one.
+// Radices below 5 (many butterflies, held over a barrier in a middle stage)
+// are first, or last in the column pass (cols), whose last stage is another
+// than its first and takes the three channels in turn.
+bool fft_plan(int n, int cnt, bool cols, uint8_t *fac, int32_t &nfac) {
+  struct Radix {
+    int p, ops;
+  };
+  static const Radix kRadices[] = {{16, 190}, {15, 200}, {12, 110}, {10, 110}, {9, 100}, {8, 64},
+                                   {7, 150},  {6, 50},   {5, 44},   {4, 18},   {3, 18},  {2, 6}};
   if (n < 1) return false;
-  std::vector<int> best(n + 1, 1 << 20), first(n + 1, 0);
+  const int threads = cols ? kFreqColThreads : kFreqRowThreads;
+  auto rounds = [&](int butterflies) { return (butterflies + threads - 1) / threads; };
+  auto cost = [&](int p, int ops, bool first, bool last) {
+    const int each = ops + 8 * p + 20, k = cnt * (n / p);
+    int c = 150 + (last && cols ? 3 * rounds(k / 3) : rounds(k)) * each;
+    if (first && p > 1) {
+      int g = 64;
+      while ((2 * p) % g) g /= 2;
+      c += rounds(k) * p * (g / 2 - 1);
+    }
+    return c;
+  };
+  // best[m]: the stages that are left when the product of those taken is n / m
+  const int kNone = 1 << 28;
+  std::vector<int> best(n + 1, kNone), next(n + 1, 0);
   best[1] = 0;
   for (int m = 2; m <= n; ++m) {
     if (n % m != 0) continue;
-    for (int p : kRadices)
-      if (m % p == 0 && best[m / p] + 1 < best[m]) {
-        best[m] = best[m / p] + 1;
-        first[m] = p;
+    for (const Radix &r : kRadices)
+      if (m % r.p == 0 && !(cols && r.p == n) && (r.p > 4 || m == n || (cols && m == r.p)) && best[m / r.p] < kNone) {
+        const int c = best[m / r.p] + cost(r.p, r.ops, m == n, m == r.p);
+        if (c < best[m]) {
+          best[m] = c;
+          next[m] = r.p;
+        }
       }
   }
-  if (best[n] > 16) return false;
   nfac = 0;
-  for (int m = n; m > 1; m /= first[m]) fac[nfac++] = (uint8_t)first[m];
+  if (n == 1 || best[n] >= kNone) {  // a lone radix, behind a first stage that only loads
+    bool ok = n == 1;
+    for (const Radix &r : kRadices) ok |= cols && r.p == n;
+    if (!ok) return false;
+    fac[nfac++] = 1;
+    if (cols) fac[nfac++] = (uint8_t)n;
+    return true;
+  }
+  for (int m = n; m > 1; m /= next[m]) {
+    if (nfac == 16) return false;
+    fac[nfac++] = (uint8_t)next[m];
+  }
   return true;
 }
 
-constexpr int kFreqMaxN = 2560;      // longest row or column transform (three LDS buffers of it)
+// Pairs of rows, or columns, per workgroup: what fits into `elems` values,
+// while that leaves `groups` workgroups of the batch's `total`.
+int freq_group(int n, int elems, int64_t total, int groups, int most) {
+  const int64_t k = std::min<int64_t>(elems / (3 * n), total / groups);
+  return (int)std::max<int64_t>(1, std::min<int64_t>(most, k));
+}
+
+// The twiddles of a transform's stages after the first.
+void fft_twiddles(const uint8_t *fac, int nfac, std::vector<float2> &tw) {
+  int Ns = fac[0];
+  for (int s = 1; s < nfac; ++s) {
+    const int P = fac[s], len = Ns * P;
+    for (int r = 1; r < P; ++r)
+      for (int k = 0; k < Ns; ++k) {
+        const double a = -2.0 * 3.14159265358979323846 * (double)(k * r) / (double)len;
+        tw.push_back(make_float2((float)std::cos(a), (float)std::sin(a)));
+      }
+    Ns = len;
+  }
+}
+
 constexpr int kFreqMaxFrames = 16384;  // frames of one scheduling step (LDS prefix sums)
 
 RigIdx rig_idx(const gsr_ctx *c) {
@@ -685,21 +742,23 @@ gsr_status gsr_freq_plan(gsr_ctx *c, const int32_t *widths, const int32_t *heigh
   if (n_images < 0) return fail(c, GSR_ERR_INVALID_ARG, "n_images < 0");
   if (n_images > 0 && (!widths || !heights)) return fail(c, GSR_ERR_INVALID_ARG, "size array is NULL");
   std::vector<FreqImg> imgs((size_t)n_images);
-  int64_t pix = 0, inter = 0, rows = 0, cols = 0;
-  int32_t max_w = 1, max_h = 1;
-  // one twiddle table exp(-2 pi i t / n) per distinct transform length,
-  // computed in double precision
+  int64_t pix = 0, inter = 0, cols = 0, row_groups = 0, col_groups = 0;
+  uint32_t lds_rows = 0, lds_cols = 0;
+  int64_t all_pairs = 0, all_cols = 0;
+  for (int32_t i = 0; i < n_images; ++i) {
+    all_pairs += ((int64_t)heights[i] + 1) / 2;
+    all_cols += (int64_t)widths[i] / 2 + 1;
+  }
+  // one twiddle table per distinct plan, computed in double precision
   std::vector<float2> tw;
-  std::vector<std::pair<int, int64_t>> tables;
-  auto table = [&](int n) -> int64_t {
+  std::vector<std::pair<std::vector<uint8_t>, int64_t>> tables;
+  auto table = [&](const uint8_t *fac, int nfac) -> int64_t {
+    const std::vector<uint8_t> key(fac, fac + nfac);
     for (const auto &t : tables)
-      if (t.first == n) return t.second;
+      if (t.first == key) return t.second;
     const int64_t off = (int64_t)tw.size();
-    for (int t = 0; t < n; ++t) {
-      const double a = -2.0 * 3.14159265358979323846 * (double)t / (double)n;
-      tw.push_back(make_float2((float)std::cos(a), (float)std::sin(a)));
-    }
-    tables.emplace_back(n, off);
+    fft_twiddles(fac, nfac, tw);
+    tables.emplace_back(key, off);
     return off;
   };
   for (int32_t i = 0; i < n_images; ++i) {
@@ -709,21 +768,27 @@ gsr_status gsr_freq_plan(gsr_ctx *c, const int32_t *widths, const int32_t *heigh
     f.h = heights[i];
     if (f.w < 1 || f.h < 1 || f.w > kFreqMaxN || f.h > kFreqMaxN)
       return fail(c, GSR_ERR_UNSUPPORTED, "image %d: %d x %d outside 1..%d", i, f.w, f.h, kFreqMaxN);
-    if (!fft_radices(f.w, f.fac_w, f.nfac_w) || !fft_radices(f.h, f.fac_h, f.nfac_h))
+    f.pairs = freq_group(f.w, kFreqRowElems, all_pairs, kFreqRowGroups, (f.h + 1) / 2);
+    while (f.pairs & (f.pairs - 1)) f.pairs &= f.pairs - 1;  // whole 32, 64, ... bytes of a column
+    f.cols = freq_group(f.h, kFreqColElems, all_cols, kFreqColGroups, f.w / 2 + 1);
+    if (!fft_plan(f.w, 3 * f.pairs, false, f.fac_w, f.nfac_w) || !fft_plan(f.h, 3 * f.cols, true, f.fac_h, f.nfac_h))
       return fail(c, GSR_ERR_UNSUPPORTED, "image %d: %d x %d has a prime factor above 7", i, f.w, f.h);
     const int64_t half = f.w / 2 + 1;
     f.pix_off = pix;
     f.inter_off = inter;
-    f.row_base = rows;
     f.col_base = cols;
-    f.tw_w = table(f.w);
-    f.tw_h = table(f.h);
+    f.row_group = row_groups;
+    f.col_group = col_groups;
+    f.tw_w = table(f.fac_w, f.nfac_w);
+    f.tw_h = table(f.fac_h, f.nfac_h);
     pix += 3ll * f.w * f.h;
-    inter += 3 * half * f.h;
-    rows += f.h;
+    inter += 3 * half * freq_pitch(f.h);
     cols += half;
-    max_w = std::max(max_w, f.w);
-    max_h = std::max(max_h, f.h);
+    row_groups += ((f.h + 1) / 2 + f.pairs - 1) / f.pairs;
+    col_groups += (half + f.cols - 1) / f.cols;
+    lds_rows = std::max(lds_rows, (uint32_t)(3 * f.pairs * f.w) * 8u);
+    lds_cols = std::max(lds_cols, (uint32_t)(3 * f.cols * f.h) * 8u +
+                                      (uint32_t)(f.cols * (f.h / f.fac_h[f.nfac_h - 1])) * 4u);
   }
   if (c->freq_d) {
     GSR_HIP(c, hipFree(c->freq_d));
@@ -734,8 +799,9 @@ gsr_status gsr_freq_plan(gsr_ctx *c, const int32_t *widths, const int32_t *heigh
     c->freq_tw_d = nullptr;
   }
   c->freq.clear();
-  c->freq_rows = c->freq_cols = c->freq_inter = 0;
+  c->freq_row_groups = c->freq_col_groups = c->freq_inter = 0;
   c->freq_ws = 0;
+  if (tw.empty()) tw.push_back(make_float2(1.0f, 0.0f));
   if (n_images > 0) {
     GSR_HIP(c, hipMalloc(&c->freq_d, imgs.size() * sizeof(FreqImg)));
     GSR_HIP(c, hipMemcpy(c->freq_d, imgs.data(), imgs.size() * sizeof(FreqImg), hipMemcpyHostToDevice));
@@ -743,11 +809,11 @@ gsr_status gsr_freq_plan(gsr_ctx *c, const int32_t *widths, const int32_t *heigh
     GSR_HIP(c, hipMemcpy(c->freq_tw_d, tw.data(), tw.size() * sizeof(float2), hipMemcpyHostToDevice));
   }
   c->freq = imgs;
-  c->freq_rows = rows;
-  c->freq_cols = cols;
+  c->freq_row_groups = row_groups;
+  c->freq_col_groups = col_groups;
   c->freq_inter = inter;
-  c->freq_max_w = max_w;
-  c->freq_max_h = max_h;
+  c->freq_lds_rows = lds_rows;
+  c->freq_lds_cols = lds_cols;
   c->freq_ws = align_up((size_t)inter * 8) + align_up((size_t)cols * 4);
   if (workspace_bytes) *workspace_bytes = c->freq_ws;
   return GSR_OK;
@@ -763,8 +829,8 @@ gsr_status gsr_freq_significance(gsr_ctx *c, const float *images, void *ws, size
   char *b = static_cast<char *>(ws);
   float2 *inter = reinterpret_cast<float2 *>(b);
   float *col_sum = reinterpret_cast<float *>(b + align_up((size_t)c->freq_inter * 8));
-  launch_freq_significance(images, c->freq_d, (int)c->freq.size(), c->freq_rows, c->freq_cols, c->freq_max_w,
-                           c->freq_max_h, c->freq_tw_d, inter, col_sum, X, static_cast<hipStream_t>(stream));
+  launch_freq_significance(images, c->freq_d, (int)c->freq.size(), c->freq_row_groups, c->freq_col_groups,
+                           c->freq_lds_rows, c->freq_lds_cols, c->freq_tw_d, inter, col_sum, X, static_cast<hipStream_t>(stream));
   GSR_HIP(c, hipGetLastError());
   return GSR_OK;
 }
