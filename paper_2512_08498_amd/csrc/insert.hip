@@ -5,14 +5,22 @@
 //   S    = d / (2 sqrt(P(I)) f) for the inserted pixel, d the distance from
 //          the back-projected centre (z from the depth map) to the camera.
 //
-// k_log_prob: one workgroup per 64 x 16 pixel tile of a view.  For each of
-// the two images a horizontal pass convolves the tile's rows and a halo of
-// R = ceil(3 sigma) rows (border pixels replicated) with the 1D Gaussian g
-// and its second derivative h, reading each item's window straight into
-// registers and leaving the results in LDS; a vertical pass finishes
-// L = (h x g + g x h) * I.  Each thread produces four pixels of one column,
-// sharing the 2R + 4 rows of the vertical window.  Writes P(I),
-// optionally P(I~), and a byte mask of the inserting pixels.
+// k_log_prob: one workgroup per tile of 64 x 32 or 64 x 16 pixels of a view.
+// For each of the two images and each channel a horizontal pass convolves the
+// tile's rows and a halo of R = ceil(3 sigma) rows (border pixels replicated)
+// with the 1D Gaussian g and its second derivative h, reading each item's
+// window straight into registers and leaving the results in LDS; a vertical
+// pass finishes L = (h x g + g x h) * I, each thread one or two rows of four
+// columns.  Writes P(I), optionally P(I~), and a byte mask of the inserting
+// pixels.
+//   Bound by VALU issue (44M instructions on six 1600x900 views; a tap of the
+// vertical pass is a product, a fused one and a sum, whose rounding the mask
+// depends on).  There 88 us; with all three channels of a 64 x 16 tile in
+// 34 KB of LDS, read a value at a time, 115, and on eight 1903x1057 views,
+// whose rows are not 16-byte aligned, the whole insertion 193 us, with their
+// windows read a value at a time 352.  Four rows per thread take 98 us (fewer
+// waves per SIMD), 64-row tiles 97 to 101; the next window or channel loaded
+// ahead 91 to 97.
 // k_ins_count / k_ins_scan / k_ins_write: stream compaction of the mask in
 // ascending pixel order (counts per 4096 pixels, one scan, then each
 // workgroup writes its pixels in order) with the new Gaussians' scale and
@@ -24,29 +32,51 @@ namespace gsr {
 
 namespace {
 
-constexpr int kTW = 64, kTH = 16;
+constexpr int kTW = 64, kTT = 256;
+// Below this many tiles of 16 rows a thread takes one row of one, above two
+// rows of one of 32, with less of a halo.  The whole insertion: one view of
+// 640x360 26 and 31 us, four of 960x540 (2,040) 43 and 46, three of 1601x901
+// (4,446) 72 and 71, six of 1600x900 110 and 104.
+constexpr uint32_t kSmallTiles = 2560;
 constexpr int kInsBlock = 4096;  // pixels per compaction workgroup (256 threads x 16)
 
+// View of a tile (the same in all lanes of the wave) and the number of tiles
+// before the view's: 64 views at a time, a lane each.
+template <int kTH>
 __device__ __forceinline__ int view_of_ins_tile(const ViewInfo *__restrict__ views, int n_views, int tile, int &base) {
+  const int lane = lane_id();
   base = 0;
-  for (int v = 0; v < n_views; ++v) {
-    const int nt = ((views[v].w + kTW - 1) / kTW) * ((views[v].h + kTH - 1) / kTH);
-    if (tile < base + nt) return v;
-    base += nt;
+  for (int v0 = 0; v0 < n_views; v0 += kWave) {
+    int nt = 0;
+    if (v0 + lane < n_views)
+      nt = ((views[v0 + lane].w + kTW - 1) / kTW) * ((views[v0 + lane].h + kTH - 1) / kTH);
+    const int incl = wave_incl_scan(nt);
+    const uint64_t past = __ballot(tile < base + incl);
+    if (past) {
+      const int l = __ffsll((unsigned long long)past) - 1;
+      base += __builtin_amdgcn_readlane(incl - nt, l);
+      return v0 + l;
+    }
+    base += __builtin_amdgcn_readlane(incl, kWave - 1);
   }
   return -1;
 }
 
+// Four floats at any float's address (one load all the same).
+struct __attribute__((packed, aligned(4))) Loose4 {
+  float x, y, z, w;
+};
+
 // R is a template parameter so that the tap loops unroll and the taps are
 // read at compile-time indices.
-template <int R>
-__global__ __launch_bounds__(256) void k_log_prob(const ViewInfo *__restrict__ views, int n_views,
-                                                  const float *__restrict__ gt, const float *__restrict__ rd,
-                                                  LogTaps taps, float tau, float *__restrict__ p_gt,
-                                                  float *__restrict__ p_rd, uint8_t *__restrict__ mask) {
-  extern __shared__ float lds[];
+// R rows to each side; tiles of kTH rows, kRows of them per thread.
+template <int R, int kTH, int kRows>
+__global__ __launch_bounds__(kTT) __attribute__((amdgpu_waves_per_eu(6))) void k_log_prob(
+    const ViewInfo *__restrict__ views, int n_views, const float *__restrict__ gt, const float *__restrict__ rd,
+    LogTaps taps, float tau, float *__restrict__ p_gt, float *__restrict__ p_rd, uint8_t *__restrict__ mask) {
   int base;
-  const int v = view_of_ins_tile(views, n_views, blockIdx.x, base);
+  static_assert(kTW / 4 * kTH / kRows == kTT);
+  const int v = view_of_ins_tile<kTH>(views, n_views, blockIdx.x, base);
   if (v < 0) return;
   const ViewInfo vi = views[v];
   const int W = vi.w, H = vi.h;
@@ -55,87 +85,122 @@ __global__ __launch_bounds__(256) void k_log_prob(const ViewInfo *__restrict__ v
   const int x0 = (t % txs) * kTW, y0 = (t / txs) * kTH;
   constexpr int rows = kTH + 2 * R;
   constexpr int RA = (R + 3) / 4 * 4;  // the filter radius rounded up to whole float4s
-  float *A = lds;                    // [3][rows][kTW]: rows * g
-  float *B = A + 3 * rows * kTW;     // [3][rows][kTW]: rows * h
-  const int x = threadIdx.x & 63, yb = (threadIdx.x >> 6) * 4;
-  float P[2][4];
+  __shared__ float4 A[rows][kTW / 4], B[rows][kTW / 4];  // rows * g, rows * h of one channel
+  const int xg = threadIdx.x & 15, yg = threadIdx.x >> 4, yb = yg * kRows;
+  // A thread's items of the horizontal pass are group xg of the rows yg,
+  // yg + kTT / 16, ...; where the tile's windows lie inside the image it reads
+  // four values at a time.
+  constexpr int kItems = (rows + kTT / 16 - 1) / (kTT / 16), kVec = (4 + 2 * RA) / 4;
+  const float *srcs[2] = {gt + 3 * vi.pix_off, rd + 3 * vi.pix_off};
+  const bool whole = x0 >= RA && x0 + kTW + RA <= W;
+  auto row_of = [&](int img, int ch, int i) {
+    const int gy = min(max(y0 + yg + i * (kTT / 16) - R, 0), H - 1);
+    return srcs[img] + ((int64_t)ch * H + gy) * W;
+  };
+  auto horizontal = [&](int r, const float *in) {
+    float a[4], b[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      a[j] = b[j] = 0.0f;
+#pragma unroll
+      for (int k = 0; k <= 2 * R; ++k) {
+        a[j] = fmaf(taps.g[k], in[j + k], a[j]);
+        b[j] = fmaf(taps.h[k], in[j + k], b[j]);
+      }
+    }
+    A[r][xg] = make_float4(a[0], a[1], a[2], a[3]);
+    B[r][xg] = make_float4(b[0], b[1], b[2], b[3]);
+  };
+  float P[2][kRows][4];
+#pragma unroll
   for (int img = 0; img < 2; ++img) {
-    const float *src = (img == 0 ? gt : rd) + 3 * vi.pix_off;
-    // horizontal pass straight from global memory: item = (row, group of
-    // four columns); its 4 + 2R inputs per channel (border replicated) are
-    // loaded into registers and give four a and four b values per channel.
-    // With 16-byte aligned rows an interior item reads whole float4s.
-    const bool vec = ((reinterpret_cast<uintptr_t>(src) | (uintptr_t)W * 4u) & 15u) == 0;
-    for (int e = threadIdx.x; e < rows * (kTW / 4); e += 256) {
-      const int r = e >> 4, c0 = (e & 15) * 4;
-      const int gy = min(max(y0 + r - R, 0), H - 1);
-      const bool interior = vec && x0 + c0 - RA >= 0 && x0 + c0 + 4 + RA <= W;
+    float L2[kRows][4];
 #pragma unroll
-      for (int ch = 0; ch < 3; ++ch) {
-        const float *row = src + ((int64_t)ch * H + gy) * W;
-        float in[4 + 2 * R];
-        if (interior) {
-          const float4 *rv = reinterpret_cast<const float4 *>(row + x0 + c0 - RA);
-          float buf[4 + 2 * RA];
+    for (int j = 0; j < kRows; ++j)
 #pragma unroll
-          for (int k = 0; k < (4 + 2 * RA) / 4; ++k) {
-            const float4 t = rv[k];
-            buf[4 * k] = t.x;
-            buf[4 * k + 1] = t.y;
-            buf[4 * k + 2] = t.z;
-            buf[4 * k + 3] = t.w;
+      for (int i = 0; i < 4; ++i) L2[j][i] = 0.0f;
+#pragma unroll 1
+    for (int c = 0; c < 3; ++c) {
+      const int ch = c == 2 ? 2 : 1 - c;  // the norm's square is l1 l1 + l0 l0 + l2 l2
+      if (whole) {
+#pragma unroll 1
+        for (int i = 0; i < kItems && yg + i * (kTT / 16) < rows; ++i) {
+          const Loose4 *rv = reinterpret_cast<const Loose4 *>(row_of(img, ch, i) + x0 + xg * 4 - RA);
+          float buf[4 * kVec];
+#pragma unroll
+          for (int k = 0; k < kVec; ++k) {
+            const Loose4 q = rv[k];
+            buf[4 * k] = q.x;
+            buf[4 * k + 1] = q.y;
+            buf[4 * k + 2] = q.z;
+            buf[4 * k + 3] = q.w;
           }
-#pragma unroll
-          for (int q = 0; q < 4 + 2 * R; ++q) in[q] = buf[q + RA - R];
-        } else {
-#pragma unroll
-          for (int q = 0; q < 4 + 2 * R; ++q) in[q] = row[min(max(x0 + c0 + q - R, 0), W - 1)];
+          horizontal(yg + i * (kTT / 16), buf + RA - R);
         }
+      } else {
+#pragma unroll 1
+        for (int i = 0; i < kItems && yg + i * (kTT / 16) < rows; ++i) {
+          const float *row = row_of(img, ch, i);
+          float in[4 + 2 * R];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          float a = 0.0f, b = 0.0f;
-#pragma unroll
-          for (int k = 0; k <= 2 * R; ++k) {
-            a += taps.g[k] * in[j + k];
-            b += taps.h[k] * in[j + k];
-          }
-          A[(ch * rows + r) * kTW + c0 + j] = a;
-          B[(ch * rows + r) * kTW + c0 + j] = b;
+          for (int q = 0; q < 4 + 2 * R; ++q) in[q] = row[min(max(x0 + xg * 4 + q - R, 0), W - 1)];
+          horizontal(yg + i * (kTT / 16), in);
         }
       }
-    }
-    __syncthreads();
-    float L2[4] = {0.f, 0.f, 0.f, 0.f};
+      __syncthreads();
+      float l[kRows][4];
 #pragma unroll
-    for (int ch = 0; ch < 3; ++ch) {
-      float l[4] = {0.f, 0.f, 0.f, 0.f};
+      for (int k = 0; k < 2 * R + kRows; ++k) {
+        const float4 a4 = A[yb + k][xg], b4 = B[yb + k][xg];
+        const float a[4] = {a4.x, a4.y, a4.z, a4.w}, b[4] = {b4.x, b4.y, b4.z, b4.w};
 #pragma unroll
-      for (int k = 0; k < 2 * R + 4; ++k) {
-        const float a = A[(ch * rows + yb + k) * kTW + x], b = B[(ch * rows + yb + k) * kTW + x];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
+        for (int j = 0; j < kRows; ++j) {
           const int kk = k - j;  // tap index of this row for output row yb + j
-          if (kk >= 0 && kk <= 2 * R) l[j] += taps.g[kk] * b + taps.h[kk] * a;
+          if (kk >= 0 && kk <= 2 * R) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              const float t = fmaf(taps.g[kk], b[i], taps.h[kk] * a[i]);
+              l[j][i] = kk == 0 ? t : l[j][i] + t;
+            }
+          }
         }
       }
 #pragma unroll
-      for (int j = 0; j < 4; ++j) L2[j] += l[j] * l[j];
+      for (int j = 0; j < kRows; ++j)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) L2[j][i] = fmaf(l[j][i], l[j][i], L2[j][i]);
+      __syncthreads();
     }
 #pragma unroll
-    for (int j = 0; j < 4; ++j) P[img][j] = fminf(sqrtf(L2[j]), 1.0f);
-    __syncthreads();
+    for (int j = 0; j < kRows; ++j)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) P[img][j][i] = fminf(sqrtf(L2[j][i]), 1.0f);
   }
-  const int gx = x0 + x;
+  const int gx = x0 + xg * 4;
   if (gx >= W) return;
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
+  for (int j = 0; j < kRows; ++j) {
     const int gy = y0 + yb + j;
     if (gy >= H) break;
     const int64_t pix = vi.pix_off + (int64_t)gy * W + gx;
-    p_gt[pix] = P[0][j];
-    if (p_rd) p_rd[pix] = P[1][j];
-    const float pa = fmaxf(P[0][j] - P[1][j], 0.0f);
-    mask[pix] = pa > tau ? 1 : 0;
+    uint32_t m[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) m[i] = fmaxf(P[0][j][i] - P[1][j][i], 0.0f) > tau ? 1u : 0u;
+    float *const p0 = p_gt + pix, *const p1 = p_rd ? p_rd + pix : p0;
+    if (gx + 4 <= W && ((reinterpret_cast<uintptr_t>(p0) | reinterpret_cast<uintptr_t>(p1)) & 15u) == 0 &&
+        (reinterpret_cast<uintptr_t>(mask + pix) & 3u) == 0) {
+      *reinterpret_cast<float4 *>(p_gt + pix) = make_float4(P[0][j][0], P[0][j][1], P[0][j][2], P[0][j][3]);
+      if (p_rd) *reinterpret_cast<float4 *>(p_rd + pix) = make_float4(P[1][j][0], P[1][j][1], P[1][j][2], P[1][j][3]);
+      *reinterpret_cast<uint32_t *>(mask + pix) = m[0] | m[1] << 8 | m[2] << 16 | m[3] << 24;
+    } else {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        if (gx + i >= W) break;
+        p_gt[pix + i] = P[0][j][i];
+        if (p_rd) p_rd[pix + i] = P[1][j][i];
+        mask[pix + i] = (uint8_t)m[i];
+      }
+    }
   }
 }
 
@@ -157,7 +222,11 @@ __global__ __launch_bounds__(256) void k_ins_count(const uint8_t *__restrict__ m
   if (threadIdx.x == 0) counts[blockIdx.x] = red[0] + red[1] + red[2] + red[3];
 }
 
-// Exclusive offsets of the blocks' counts and the total (one workgroup).
+// Exclusive offsets of the blocks' counts and the total (one workgroup), for
+// more than kSumBlocks blocks; up to there k_ins_write adds the counts of the
+// blocks before its own itself: on six 1600x900 views (2,110 blocks) 0.7 us
+// there for a launch of 4.8.
+constexpr uint32_t kSumBlocks = 4096;
 __global__ __launch_bounds__(1024) void k_ins_scan(const uint32_t *__restrict__ counts, uint32_t nb,
                                                    uint32_t *__restrict__ offsets, uint32_t *__restrict__ total) {
   __shared__ uint32_t wsum[16];
@@ -194,9 +263,11 @@ __global__ __launch_bounds__(1024) void k_ins_scan(const uint32_t *__restrict__ 
   }
 }
 
+template <bool SUM>
 __global__ __launch_bounds__(256) void k_ins_write(const ViewInfo *__restrict__ views, int n_views,
                                                    const Cam *__restrict__ cams, const uint8_t *__restrict__ mask,
-                                                   int64_t n_pix, const uint32_t *__restrict__ offsets,
+                                                   int64_t n_pix, const uint32_t *__restrict__ counts,
+                                                   const uint32_t *__restrict__ offsets, uint32_t *__restrict__ total,
                                                    const float *__restrict__ p_gt, const float *__restrict__ depth,
                                                    uint32_t *__restrict__ out_pix, float *__restrict__ out_scale,
                                                    float *__restrict__ out_mean, int64_t capacity) {
@@ -216,7 +287,17 @@ __global__ __launch_bounds__(256) void k_ins_write(const ViewInfo *__restrict__ 
   const uint32_t mine = __popc(bits);
   uint32_t block_total;
   const uint32_t before = block_excl_scan<256>(mine, scan_tmp, block_total);
-  uint32_t k = offsets[blockIdx.x] + before;
+  uint32_t first;
+  if (SUM) {
+    uint32_t s = 0;
+    for (uint32_t b = threadIdx.x; b < blockIdx.x; b += 256) s += counts[b];
+    __syncthreads();
+    (void)block_excl_scan<256>(s, scan_tmp, first);
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) *total = first + block_total;
+  } else {
+    first = offsets[blockIdx.x];
+  }
+  uint32_t k = first + before;
   if (bits == 0) return;
   // view of the thread's first pixel (binary search), then forward at the
   // (rare) view boundary inside its 16 pixels
@@ -259,30 +340,32 @@ __global__ __launch_bounds__(256) void k_ins_write(const ViewInfo *__restrict__ 
 
 }  // namespace
 
-uint32_t ins_tiles(const ViewInfo *views_host, int n_views) {
-  uint32_t n = 0;
-  for (int v = 0; v < n_views; ++v)
-    n += (uint32_t)(((views_host[v].w + kTW - 1) / kTW) * ((views_host[v].h + kTH - 1) / kTH));
-  return n;
+uint32_t ins_tiles(const ViewInfo *views_host, int n_views, bool &small) {
+  auto tiles = [&](int th) {
+    uint32_t n = 0;
+    for (int v = 0; v < n_views; ++v)
+      n += (uint32_t)(((views_host[v].w + kTW - 1) / kTW) * ((views_host[v].h + th - 1) / th));
+    return n;
+  };
+  const uint32_t n = tiles(16);
+  small = n < kSmallTiles;
+  return small ? n : tiles(32);
 }
 
 uint32_t ins_blocks(int64_t n_pix) { return (uint32_t)((n_pix + kInsBlock - 1) / kInsBlock); }
 
-size_t ins_lds_bytes(int R) {
-  const int rows = kTH + 2 * R;
-  return (size_t)(2 * 3 * rows * kTW) * sizeof(float);
-}
-
-void launch_log_insert(const ViewInfo *views_d, int n_views, uint32_t n_tiles, int64_t n_pix, const Cam *cams,
+void launch_log_insert(const ViewInfo *views_d, int n_views, uint32_t n_tiles, bool small, int64_t n_pix, const Cam *cams,
                        const float *gt, const float *rd, const float *depth, const LogTaps &taps, float tau,
                        float *p_gt, float *p_rd, uint8_t *mask, uint32_t *counts, uint32_t *offsets,
                        uint32_t *total, uint32_t *out_pix, float *out_scale, float *out_mean, int64_t capacity,
                        hipStream_t st) {
   if (n_tiles == 0) return;
-#define GSR_LOG_PROB(RR)                                                                                    \
-  case RR:                                                                                                  \
-    k_log_prob<RR><<<n_tiles, 256, ins_lds_bytes(RR), st>>>(views_d, n_views, gt, rd, taps, tau, p_gt, p_rd, \
-                                                            mask);                                          \
+#define GSR_LOG_PROB(RR)                                                                                          \
+  case RR:                                                                                                        \
+    if (small)                                                                                                    \
+      k_log_prob<RR, 16, 1><<<n_tiles, kTT, 0, st>>>(views_d, n_views, gt, rd, taps, tau, p_gt, p_rd, mask);       \
+    else                                                                                                          \
+      k_log_prob<RR, 32, 2><<<n_tiles, kTT, 0, st>>>(views_d, n_views, gt, rd, taps, tau, p_gt, p_rd, mask);       \
     break;
   switch (taps.R) {
     GSR_LOG_PROB(1)
@@ -294,9 +377,14 @@ void launch_log_insert(const ViewInfo *views_d, int n_views, uint32_t n_tiles, i
 #undef GSR_LOG_PROB
   const uint32_t nb = ins_blocks(n_pix);
   k_ins_count<<<nb, 256, 0, st>>>(mask, n_pix, counts);
+  if (nb <= kSumBlocks) {
+    k_ins_write<true><<<nb, 256, 0, st>>>(views_d, n_views, cams, mask, n_pix, counts, offsets, total, p_gt, depth,
+                                          out_pix, out_scale, out_mean, capacity);
+    return;
+  }
   k_ins_scan<<<1, 1024, 0, st>>>(counts, nb, offsets, total);
-  k_ins_write<<<nb, 256, 0, st>>>(views_d, n_views, cams, mask, n_pix, offsets, p_gt, depth, out_pix, out_scale,
-                                  out_mean, capacity);
+  k_ins_write<false><<<nb, 256, 0, st>>>(views_d, n_views, cams, mask, n_pix, counts, offsets, total, p_gt, depth,
+                                         out_pix, out_scale, out_mean, capacity);
 }
 
 }  // namespace gsr

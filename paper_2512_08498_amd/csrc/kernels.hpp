@@ -100,10 +100,9 @@ uint32_t cam_chunks(uint32_t cap_rec);
 void launch_freq_significance(const float *images, const FreqImg *imgs, int n_imgs, int64_t row_groups,
                               int64_t col_groups, uint32_t lds_rows, uint32_t lds_cols, const float2 *tw, float2 *inter,
                               float *col_sum, float *X, hipStream_t st);
-uint32_t ins_tiles(const ViewInfo *views_host, int n_views);
+uint32_t ins_tiles(const ViewInfo *views_host, int n_views, bool &small);
 uint32_t ins_blocks(int64_t n_pix);
-size_t ins_lds_bytes(int R);
-void launch_log_insert(const ViewInfo *views_d, int n_views, uint32_t n_tiles, int64_t n_pix, const Cam *cams,
+void launch_log_insert(const ViewInfo *views_d, int n_views, uint32_t n_tiles, bool small, int64_t n_pix, const Cam *cams,
                        const float *gt, const float *rd, const float *depth, const LogTaps &taps, float tau,
                        float *p_gt, float *p_rd, uint8_t *mask, uint32_t *counts, uint32_t *offsets,
                        uint32_t *total, uint32_t *out_pix, float *out_scale, float *out_mean, int64_t capacity,

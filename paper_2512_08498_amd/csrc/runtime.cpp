@@ -933,7 +933,9 @@ gsr_status gsr_log_insert(gsr_ctx *c, const gsr_camera *cams, const float *gt, c
   taps.R = R;
   const int64_t px = total_px(c);
   char *b = static_cast<char *>(ws);
-  launch_log_insert(c->views_d, c->n_views, ins_tiles(c->views.data(), c->n_views), px,
+  bool small = false;
+  const uint32_t tiles = ins_tiles(c->views.data(), c->n_views, small);
+  launch_log_insert(c->views_d, c->n_views, tiles, small, px,
                     reinterpret_cast<const Cam *>(cams), gt, render, depth, taps, cfg->tau_a, p_gt, p_render,
                     reinterpret_cast<uint8_t *>(b + L.mask), reinterpret_cast<uint32_t *>(b + L.counts),
                     reinterpret_cast<uint32_t *>(b + L.offsets), out->count, out->pix, out->scale, out->mean,
