@@ -23,12 +23,16 @@
 
 namespace gsr {
 
+__device__ __forceinline__ void adam_move(float &p, float m, float v, float lr, float eps, float bc1, float bc2) {
+  const float mh = m / bc1, vh = v / bc2;
+  p = p - lr * mh / (sqrtf(vh) + eps);
+}
+
 __device__ __forceinline__ void adam_update(float &p, float &m, float &v, float g, float lr, float b1, float b2,
                                             float eps, float bc1, float bc2) {
   m = b1 * m + (1.0f - b1) * g;
   v = b2 * v + (1.0f - b2) * g * g;
-  const float mh = m / bc1, vh = v / bc2;
-  p = p - lr * mh / (sqrtf(vh) + eps);
+  adam_move(p, m, v, lr, eps, bc1, bc2);
 }
 
 __device__ __forceinline__ void bias_corrections(const AdamArgs &a, float &bc1, float &bc2) {
@@ -386,35 +390,87 @@ __global__ void k_step_inc(int32_t *step) {
   if (threadIdx.x == 0 && blockIdx.x == 0) *step += 1;
 }
 
-// Dense Adam over the six parameter groups in one launch.
+// Dense Adam over the six parameter groups in one launch: a workgroup takes
+// kAdamPer values of one group, four neighbours per thread and access.  HBM
+// bounds it (28 bytes per value): 1M Gaussians of degree 3, 1.65 GB, 263 us (6.3
+// TB/s); with a value per access and a search of its group each, 338.
 struct AdamSeg {
   float *p, *g, *m, *v;
   int64_t count;
   float lr;
+  uint32_t first;  // the group's first workgroup
 };
 struct AdamSegs {
   AdamSeg s[6];
 };
+constexpr int kAdamPer = 1024;
+// From this many values on (16 bytes of state each) loads and stores bypass
+// the caches, which then hold too little of the state for the next step to
+// find it: repeated steps of 400k Gaussians of degree 3 (24M values) take 116
+// us through the caches and 121 past them, of 600k (35M) 193 and 164, of 1M 309
+// and 276 (two launches).
+constexpr int64_t kAdamStream = 28'000'000;
 
-__global__ __launch_bounds__(256) void k_adam(AdamSegs segs, float b1, float b2, float eps, const int32_t *step,
-                                               int64_t total) {
+// Four neighbours, through the caches or past them (STREAM).
+template <bool STREAM>
+__device__ __forceinline__ void load4(float (&x)[4], const float *p) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) x[i] = STREAM ? __builtin_nontemporal_load(p + i) : p[i];
+}
+template <bool STREAM>
+__device__ __forceinline__ void store4(float *p, const float (&x)[4]) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    if (STREAM) __builtin_nontemporal_store(x[i], p + i);
+    else p[i] = x[i];
+  }
+}
+
+template <bool STREAM>
+__global__ __launch_bounds__(256) void k_adam(AdamSegs segs, float b1, float b2, float eps, const int32_t *step) {
+  int k = 0;
+  while (k < 5 && blockIdx.x >= segs.s[k + 1].first) ++k;
+  const AdamSeg &S = segs.s[k];
+  const int64_t j = (int64_t)(blockIdx.x - S.first) * kAdamPer + threadIdx.x * 4;
+  const int64_t left = S.count - j;
+  if (left <= 0) return;
+  float p[4], g[4], m[4], v[4];
+  if (left >= 4) {
+    load4<STREAM>(p, S.p + j);
+    load4<STREAM>(g, S.g + j);
+    load4<STREAM>(m, S.m + j);
+    load4<STREAM>(v, S.v + j);
+  } else {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int64_t q = i < left ? j + i : j;
+      p[i] = S.p[q];
+      g[i] = S.g[q];
+      m[i] = S.m[q];
+      v[i] = S.v[q];
+    }
+  }
   const float t = (float)(*step);
   const float bc1 = 1.0f - exp2f(t * log2f(b1));
   const float bc2 = 1.0f - exp2f(t * log2f(b2));
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += stride) {
-    int64_t j = i;
-    int s = 0;
-    while (s < 5 && j >= segs.s[s].count) {
-      j -= segs.s[s].count;
-      ++s;
-    }
-    const AdamSeg &S = segs.s[s];
-    float p = S.p[j], m = S.m[j], v = S.v[j];
-    adam_update(p, m, v, S.g[j], S.lr, b1, b2, eps, bc1, bc2);
-    S.p[j] = p;
-    S.m[j] = m;
-    S.v[j] = v;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    m[i] = fmaf(b1, m[i], (1.0f - b1) * g[i]);
+    v[i] = fmaf(b2, v[i], (1.0f - b2) * g[i] * g[i]);
+    adam_move(p[i], m[i], v[i], S.lr, eps, bc1, bc2);
+  }
+  if (left >= 4) {
+    store4<STREAM>(S.p + j, p);
+    store4<STREAM>(S.m + j, m);
+    store4<STREAM>(S.v + j, v);
+  } else {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (i < left) {
+        S.p[j + i] = p[i];
+        S.m[j + i] = m[i];
+        S.v[j + i] = v[i];
+      }
   }
 }
 
@@ -451,16 +507,22 @@ void launch_step_inc(int32_t *step, hipStream_t st) { k_step_inc<<<1, 64, 0, st>
 void launch_adam(const MutPtrs &g, const AdamArgs &a, int64_t n, int sh_degree, hipStream_t st) {
   const int64_t K = (int64_t)(sh_degree + 1) * (sh_degree + 1);
   AdamSegs s;
-  s.s[0] = {a.p.mean, g.mean, a.m.mean, a.v.mean, 3 * n, a.lr[0]};
-  s.s[1] = {a.p.log_scale, g.log_scale, a.m.log_scale, a.v.log_scale, 3 * n, a.lr[1]};
-  s.s[2] = {a.p.quat, g.quat, a.m.quat, a.v.quat, 4 * n, a.lr[2]};
-  s.s[3] = {a.p.opacity_logit, g.opacity_logit, a.m.opacity_logit, a.v.opacity_logit, n, a.lr[3]};
-  s.s[4] = {a.p.sh, g.sh, a.m.sh, a.v.sh, 3 * n, a.lr[4]};
-  s.s[5] = {a.p.sh + 3 * n, g.sh + 3 * n, a.m.sh + 3 * n, a.v.sh + 3 * n, (K - 1) * 3 * n, a.lr[5]};
-  const int64_t total = (11 + 3 * K) * n;
-  if (total == 0) return;
-  const int64_t blocks = std::min<int64_t>((total + 255) / 256, 16384);
-  k_adam<<<(unsigned)blocks, 256, 0, st>>>(s, a.beta1, a.beta2, a.eps, a.step, total);
+  s.s[0] = {a.p.mean, g.mean, a.m.mean, a.v.mean, 3 * n, a.lr[0], 0u};
+  s.s[1] = {a.p.log_scale, g.log_scale, a.m.log_scale, a.v.log_scale, 3 * n, a.lr[1], 0u};
+  s.s[2] = {a.p.quat, g.quat, a.m.quat, a.v.quat, 4 * n, a.lr[2], 0u};
+  s.s[3] = {a.p.opacity_logit, g.opacity_logit, a.m.opacity_logit, a.v.opacity_logit, n, a.lr[3], 0u};
+  s.s[4] = {a.p.sh, g.sh, a.m.sh, a.v.sh, 3 * n, a.lr[4], 0u};
+  s.s[5] = {a.p.sh + 3 * n, g.sh + 3 * n, a.m.sh + 3 * n, a.v.sh + 3 * n, (K - 1) * 3 * n, a.lr[5], 0u};
+  uint32_t blocks = 0;
+  for (AdamSeg &g6 : s.s) {
+    g6.first = blocks;
+    blocks += (uint32_t)((g6.count + kAdamPer - 1) / kAdamPer);
+  }
+  if (blocks == 0) return;
+  if ((11 + 3 * K) * n >= kAdamStream)
+    k_adam<true><<<blocks, 256, 0, st>>>(s, a.beta1, a.beta2, a.eps, a.step);
+  else
+    k_adam<false><<<blocks, 256, 0, st>>>(s, a.beta1, a.beta2, a.eps, a.step);
 }
 
 }  // namespace gsr

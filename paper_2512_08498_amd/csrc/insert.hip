@@ -62,11 +62,6 @@ __device__ __forceinline__ int view_of_ins_tile(const ViewInfo *__restrict__ vie
   return -1;
 }
 
-// Four floats at any float's address (one load all the same).
-struct __attribute__((packed, aligned(4))) Loose4 {
-  float x, y, z, w;
-};
-
 // R is a template parameter so that the tap loops unroll and the taps are
 // read at compile-time indices.
 // R rows to each side; tiles of kTH rows, kRows of them per thread.

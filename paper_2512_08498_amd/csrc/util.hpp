@@ -42,6 +42,11 @@ __device__ __forceinline__ T block_excl_scan(T x, T *lds, T &total) {
   return before + incl - x;
 }
 
+// Four floats at any float's address (one load or store all the same).
+struct __attribute__((packed, aligned(4))) Loose4 {
+  float x, y, z, w;
+};
+
 template <typename T>
 __device__ __forceinline__ T wave_reduce_or(T x) {
 #pragma unroll
