@@ -70,7 +70,27 @@ struct GroupN {
 // Three waves per SIMD: the CAM variant's extra live values would otherwise
 // push the degree-3 kernel past 168 registers and down to one or two waves,
 // which costs more than the few spills that keep it at three.
-template <int DEG, bool ADAM, bool CAM>
+// What passes the caches by, from this many parameter values of the state on:
+// the moments, which nothing else reads, and the parameters, which the next
+// forward reads first.  A training step of two 960x540 views (before, moments
+// past the caches, both): 200k Gaussians of degree 3 (12M values) 404, 406 and
+// 409 us, 300k 596, 585 and 588, 600k (35M) 1033, 996 and 1007; of four views,
+// 1M (59M) 1666, 1623 and 1602, 2M 3183, 3109 and 3050.
+constexpr int64_t kStreamMoments = 16'000'000, kStreamParams = 48'000'000;
+
+template <bool STREAM>
+__device__ __forceinline__ float load_past(const float *p) {
+  return STREAM ? __builtin_nontemporal_load(p) : *p;
+}
+template <bool STREAM>
+__device__ __forceinline__ void store_past(float *p, float x) {
+  if (STREAM) __builtin_nontemporal_store(x, p);
+  else *p = x;
+}
+
+// ADAM: 0 gradients only, 1 with the update, 2 the moments and 3 the
+// parameters too past the caches.
+template <int DEG, int ADAM, bool CAM>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_pre_bwd(
     GaussPtrs gp, const Cam *__restrict__ cams, Ws ws, Sizes sz, MutPtrs grads, int accumulate, AdamArgs adam,
     float4 *__restrict__ cam_rec) {
@@ -225,8 +245,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
 #pragma unroll
     for (int i = 0; i < decltype(tag)::N; ++i) {
       pp[i] = adam.p_is_g ? pv[i] : p[off[i]];
-      mm[i] = m[off[i]];
-      vv[i] = v[off[i]];
+      mm[i] = load_past<ADAM >= 2>(m + off[i]);
+      vv[i] = load_past<ADAM >= 2>(v + off[i]);
     }
   };
   auto adam_store = [&](auto tag, float *p, float *m, float *v, float *gout, const int64_t(&off)[decltype(tag)::N],
@@ -237,9 +257,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
     for (int i = 0; i < N; ++i) adam_update(pp[i], mm[i], vv[i], gv[i], lr[i], adam.beta1, adam.beta2, adam.eps, bc1, bc2);
 #pragma unroll
     for (int i = 0; i < N; ++i) {
-      p[off[i]] = pp[i];
-      m[off[i]] = mm[i];
-      v[off[i]] = vv[i];
+      store_past<ADAM >= 3>(p + off[i], pp[i]);
+      store_past<ADAM >= 2>(m + off[i], mm[i]);
+      store_past<ADAM >= 2>(v + off[i], vv[i]);
       if (gout) gout[off[i]] = gv[i];
     }
   };
@@ -277,7 +297,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
 #pragma unroll
   for (int k = 0; k < K; ++k)
 #pragma unroll
-    for (int ch = 0; ch < 3; ++ch) shv[k][ch] = gp.sh[((int64_t)k * 3 + ch) * n + g];
+    for (int ch = 0; ch < 3; ++ch) shv[k][ch] = load_past<ADAM >= 3>(gp.sh + ((int64_t)k * 3 + ch) * n + g);
   __shared__ float a_lds[3 * K][256];
   const int tc = (int)threadIdx.x;
 #pragma unroll
@@ -411,19 +431,16 @@ constexpr int kAdamPer = 1024;
 // and 276 (two launches).
 constexpr int64_t kAdamStream = 28'000'000;
 
-// Four neighbours, through the caches or past them (STREAM).
+// Four neighbours.
 template <bool STREAM>
 __device__ __forceinline__ void load4(float (&x)[4], const float *p) {
 #pragma unroll
-  for (int i = 0; i < 4; ++i) x[i] = STREAM ? __builtin_nontemporal_load(p + i) : p[i];
+  for (int i = 0; i < 4; ++i) x[i] = load_past<STREAM>(p + i);
 }
 template <bool STREAM>
 __device__ __forceinline__ void store4(float *p, const float (&x)[4]) {
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    if (STREAM) __builtin_nontemporal_store(x[i], p + i);
-    else p[i] = x[i];
-  }
+  for (int i = 0; i < 4; ++i) store_past<STREAM>(p + i, x[i]);
 }
 
 template <bool STREAM>
@@ -481,16 +498,19 @@ void launch_pre_bwd(const GaussPtrs &gp, const Cam *cams, const Ws &ws, const Si
   MutPtrs gr = grads ? *grads : MutPtrs{nullptr, nullptr, nullptr, nullptr, nullptr};
   AdamArgs a{};
   if (adam) a = *adam;
+  const int64_t values = (int64_t)(11 + 3 * (sh_degree + 1) * (sh_degree + 1)) * sz.n;
+  const int mode = !adam ? 0 : values >= kStreamParams ? 3 : values >= kStreamMoments ? 2 : 1;
 #define GSR_PRE_BWD_C(D, A)                                                                        \
   if (cam_rec)                                                                                     \
     k_pre_bwd<D, A, true><<<blocks, 256, 0, st>>>(gp, cams, ws, sz, gr, accumulate, a, cam_rec);   \
   else                                                                                             \
     k_pre_bwd<D, A, false><<<blocks, 256, 0, st>>>(gp, cams, ws, sz, gr, accumulate, a, nullptr);
-#define GSR_PRE_BWD(D)      \
-  if (adam) {               \
-    GSR_PRE_BWD_C(D, true)  \
-  } else {                  \
-    GSR_PRE_BWD_C(D, false) \
+#define GSR_PRE_BWD(D)                  \
+  switch (mode) {                       \
+    case 0: GSR_PRE_BWD_C(D, 0) break;  \
+    case 1: GSR_PRE_BWD_C(D, 1) break;  \
+    case 2: GSR_PRE_BWD_C(D, 2) break;  \
+    default: GSR_PRE_BWD_C(D, 3) break; \
   }
   switch (sh_degree) {
     case 0: GSR_PRE_BWD(0) break;

@@ -38,3 +38,33 @@ def test_adam_sizes(n, degree):
             p = p - rate * (m / (1 - b1**t)) / ((v / (1 - b2**t)).sqrt() + eps)
         bound = steps * (1e-4 * float(rate.max()) + float(p.abs().max()) * 2.0**-24)
         assert float((params[a].double() - p).abs().max()) <= bound, a
+
+
+@pytest.mark.parametrize("n, degree", [(271_186, 3), (271_187, 3), (813_560, 3), (1_142_858, 0)])
+def test_fused_step_past_the_caches(n, degree):
+    """The fused step at the sizes from which its moments, then its parameters
+    pass the caches by, against the backward and the dense step (the same
+    formula on the same gradients), and the next forward, which reads what the
+    step has written."""
+    g = torch.Generator("cuda").manual_seed(n)
+    k = (degree + 1) ** 2
+
+    def normal(*shape, sd=1.0):
+        return torch.randn(*shape, generator=g, device="cuda") * sd
+
+    params = dict(mean=normal(3, n), log_scale=normal(3, n, sd=0.3) - 5.0, quat=normal(4, n), opacity_logit=normal(n),
+                  sh=normal(k, 3, n, sd=0.3))
+    params["mean"][2] += 5.0
+    rast = Rasterizer([camera(f=200.0, w=160, h=120)], n, degree, capacity_pairs=20 * n)
+    out = rast.forward(params)
+    dl = normal(3 * rast.total_px, sd=1e-4)
+    grads = rast.backward(params, out, dl)
+    apart = {a: t.clone() for a, t in params.items()}
+    dense = FusedAdam(rast, apart)
+    dense.apply(grads)
+    fused = FusedAdam(rast, params)
+    rast.backward_adam(params, out, dl, fused)
+    for a in params:
+        assert torch.allclose(params[a], apart[a], rtol=0, atol=1e-7), a
+        assert torch.equal(fused.m[a], dense.m[a]), a
+    assert torch.allclose(rast.forward(params)["image"], rast.forward(apart)["image"], rtol=0, atol=1e-4)
