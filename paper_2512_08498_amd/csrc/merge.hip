@@ -27,8 +27,8 @@
 //                     of other pixels are stale, rejected by the match), group init
 //   k_merge_match     one thread per Gaussian: projection, correspondence,
 //                     group accumulation
-//   k_merge_samples   the samples of the view (grid-stride): keep / colour / centre
-//   k_merge_gaussians one thread per Gaussian: keep / colour / centre
+//   k_merge_out       the samples of the view (grid-stride) and one thread per
+//                     Gaussian: keep / colour / centre
 #include <algorithm>
 
 #include "kernels.hpp"
@@ -119,8 +119,6 @@ __global__ __launch_bounds__(256) void k_merge_match(GaussPtrs gp, int64_t n, co
       for (int q = 0; q < 4; ++q) {
         const int i = i0 + (q & 1), j = j0 + (q >> 1);
         const double w = ((q & 1) ? al : 1.0 - al) * ((q >> 1) ? be : 1.0 - be);
-        const int ic = min(max(i, 0), W - 1), jc = min(max(j, 0), H - 1);
-        pv[q] = (double)p_gt[vi.pix_off + (uint32_t)(jc * W + ic)];
         if (i >= 0 && i < W && j >= 0 && j < H && w > best_w) {
           // the slot map is not cleared between calls: an entry counts only
           // if it names a live sample whose pixel is this one (each pixel is
@@ -136,6 +134,13 @@ __global__ __launch_bounds__(256) void k_merge_match(GaussPtrs gp, int64_t n, co
       }
       if (best_k >= 0 && fabs(dg - sample_dist(c, s_mean, best_k)) <= (double)tau_d) {
         m = best_p;
+        // P only here: gathered for every Gaussian in view it cost 6 of 23 us
+        // (1M Gaussians)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int ic = min(max(i0 + (q & 1), 0), W - 1), jc = min(max(j0 + (q >> 1), 0), H - 1);
+          pv[q] = (double)p_gt[vi.pix_off + (uint32_t)(jc * W + ic)];
+        }
         const double p_at = (1.0 - be) * ((1.0 - al) * pv[0] + al * pv[1]) + be * ((1.0 - al) * pv[2] + al * pv[3]);
         const double ls = ((double)gp.log_scale[g] + (double)gp.log_scale[n + g] + (double)gp.log_scale[2 * n + g]) / 3.0;
         const double rho = (double)kappa * exp(ls) * (double)c.fx / dg * 2.0 * sqrt(p_at);
@@ -166,17 +171,18 @@ __device__ __forceinline__ bool existing_wins(const u64 *win, uint32_t p) {
   return __uint_as_float((uint32_t)(win[p] >> 32)) <= 1.0f;
 }
 
-__global__ __launch_bounds__(256) void k_merge_samples(const Cam *__restrict__ cams, int view,
-                                                       const uint32_t *__restrict__ pix,
-                                                       const uint32_t *__restrict__ count, int64_t capacity,
-                                                       uint32_t off, uint32_t npx, const float *__restrict__ gt,
-                                                       const float *__restrict__ s_mean,
-                                                       const uint32_t *__restrict__ cnt, const u64 *__restrict__ csum,
-                                                       const u64 *__restrict__ dsum, const u64 *__restrict__ win,
-                                                       uint8_t *__restrict__ keep_new, float *__restrict__ colour_new,
-                                                       float *__restrict__ mean_new) {
+// The samples of the view, by `blocks` workgroups: keep / colour / centre.
+__device__ __forceinline__ void merge_samples(uint32_t block, uint32_t blocks, const Cam *__restrict__ cams, int view,
+                                              const uint32_t *__restrict__ pix,
+                                              const uint32_t *__restrict__ count, int64_t capacity,
+                                              uint32_t off, uint32_t npx, const float *__restrict__ gt,
+                                              const float *__restrict__ s_mean,
+                                              const uint32_t *__restrict__ cnt, const u64 *__restrict__ csum,
+                                              const u64 *__restrict__ dsum, const u64 *__restrict__ win,
+                                              uint8_t *__restrict__ keep_new, float *__restrict__ colour_new,
+                                              float *__restrict__ mean_new) {
   const int64_t nk = min((int64_t)*count, capacity);
-  for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < nk; k += (int64_t)gridDim.x * blockDim.x) {
+  for (int64_t k = (int64_t)block * blockDim.x + threadIdx.x; k < nk; k += (int64_t)blocks * blockDim.x) {
     const uint32_t gpix = pix[k], p = gpix - off;
     if (gpix < off || p >= npx) continue;
     float cs[3];
@@ -202,16 +208,17 @@ __global__ __launch_bounds__(256) void k_merge_samples(const Cam *__restrict__ c
   }
 }
 
-__global__ __launch_bounds__(256) void k_merge_gaussians(GaussPtrs gp, int64_t n, const Cam *__restrict__ cams,
-                                                         int view, uint32_t off, uint32_t npx,
-                                                         const int32_t *__restrict__ match,
-                                                         const int32_t *__restrict__ slot,
-                                                         const float *__restrict__ gt, const float *__restrict__ s_mean,
-                                                         const uint32_t *__restrict__ cnt,
-                                                         const u64 *__restrict__ csum, const u64 *__restrict__ dsum,
-                                                         const u64 *__restrict__ win, uint8_t *__restrict__ keep,
-                                                         float *__restrict__ colour, float *__restrict__ mean_out) {
-  const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+// One thread per Gaussian: keep / colour / centre.
+__device__ __forceinline__ void merge_gaussians(uint32_t block, GaussPtrs gp, int64_t n, const Cam *__restrict__ cams,
+                                              int view, uint32_t off, uint32_t npx,
+                                              const int32_t *__restrict__ match,
+                                              const int32_t *__restrict__ slot,
+                                              const float *__restrict__ gt, const float *__restrict__ s_mean,
+                                              const uint32_t *__restrict__ cnt,
+                                              const u64 *__restrict__ csum, const u64 *__restrict__ dsum,
+                                              const u64 *__restrict__ win, uint8_t *__restrict__ keep,
+                                              float *__restrict__ colour, float *__restrict__ mean_out) {
+  const int64_t g = (int64_t)block * blockDim.x + threadIdx.x;
   if (g >= n) return;
   float own[3];
 #pragma unroll
@@ -244,6 +251,24 @@ __global__ __launch_bounds__(256) void k_merge_gaussians(GaussPtrs gp, int64_t n
   }
 }
 
+// Both, the samples' workgroups first: either is mostly a launch's own time
+// (1M Gaussians and one view's samples 10.5 and 5.7 us apart, 11.9 in one).
+__global__ __launch_bounds__(256) void k_merge_out(
+    uint32_t sample_blocks, GaussPtrs gp, int64_t n, const Cam *__restrict__ cams, int view,
+    const uint32_t *__restrict__ pix, const uint32_t *__restrict__ count, int64_t capacity, uint32_t off, uint32_t npx,
+    const int32_t *__restrict__ match, const int32_t *__restrict__ slot, const float *__restrict__ gt,
+    const float *__restrict__ s_mean, const uint32_t *__restrict__ cnt, const u64 *__restrict__ csum,
+    const u64 *__restrict__ dsum, const u64 *__restrict__ win, uint8_t *__restrict__ keep, float *__restrict__ colour,
+    float *__restrict__ mean_out, uint8_t *__restrict__ keep_new, float *__restrict__ colour_new,
+    float *__restrict__ mean_new) {
+  if (blockIdx.x < sample_blocks)
+    merge_samples(blockIdx.x, sample_blocks, cams, view, pix, count, capacity, off, npx, gt, s_mean, cnt, csum, dsum,
+                  win, keep_new, colour_new, mean_new);
+  else
+    merge_gaussians(blockIdx.x - sample_blocks, gp, n, cams, view, off, npx, match, slot, gt, s_mean, cnt, csum, dsum,
+                    win, keep, colour, mean_out);
+}
+
 }  // namespace
 
 void launch_merge(const GaussPtrs &gp, int64_t n, const Cam *cams, int view, const ViewInfo &vi, const float *gt,
@@ -261,13 +286,11 @@ void launch_merge(const GaussPtrs &gp, int64_t n, const Cam *cams, int view, con
     k_merge_match<<<(unsigned)((n + 255) / 256), 256, 0, st>>>(gp, n, cams, view, vi, mb.slot, pix, count, capacity,
                                                                s_mean, p_gt, tau_d, kappa, mb.match, mb.cnt, mb.csum,
                                                                mb.dsum, mb.win);
-  if (capacity > 0)
-    k_merge_samples<<<sgrid, 256, 0, st>>>(cams, view, pix, count, capacity, vi.pix_off, npx, gt, s_mean, mb.cnt,
-                                           mb.csum, mb.dsum, mb.win, keep_new, colour_new, mean_new);
-  if (n > 0)
-    k_merge_gaussians<<<(unsigned)((n + 255) / 256), 256, 0, st>>>(gp, n, cams, view, vi.pix_off, npx, mb.match,
-                                                                   mb.slot, gt, s_mean, mb.cnt, mb.csum, mb.dsum,
-                                                                   mb.win, keep, colour, mean_out);
+  const unsigned gblocks = (unsigned)((n + 255) / 256), sblocks = capacity > 0 ? sgrid : 0u;
+  if (gblocks + sblocks > 0)
+    k_merge_out<<<sblocks + gblocks, 256, 0, st>>>(sblocks, gp, n, cams, view, pix, count, capacity, vi.pix_off, npx,
+                                                   mb.match, mb.slot, gt, s_mean, mb.cnt, mb.csum, mb.dsum, mb.win,
+                                                   keep, colour, mean_out, keep_new, colour_new, mean_new);
 }
 
 }  // namespace gsr
