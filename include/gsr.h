@@ -297,7 +297,8 @@ gsr_status gsr_profile_read(gsr_ctx *ctx, double *ms, int64_t *calls, int32_t re
  *             four tiles per workgroup.  Below 32: lists of at least this many
  *             entries are long (0: every tile's).  From 32 on: those of at
  *             least a 4096th of the batch's pairs and 32 entries, which would
- *             outlast the rest of the launch.
+ *             outlast the rest of the launch.  In batches of at most 6,144
+ *             tiles all are.
  *  persistent 0: one workgroup per work item (a tile, or at 16 px a group
  *             of four short tiles), dispatched by the hardware in the
  *             longest-first order.  1: a persistent launch of as many

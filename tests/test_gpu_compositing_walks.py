@@ -48,9 +48,9 @@ def test_forward_groups_agree_bitwise(ts, n, opacity_mean):
     log(f"ts {ts}, {n} Gaussians: longest walk {int(a['last_pos'].max())}, {int(a['n_contrib'].max())} composited")
 
 
-def _grads(sc, params, cam, ts, long_list, spoil):
-    rast = Rasterizer([cam], sc.n, sc.sh_degree, tile_size=ts, long_list=long_list, capacity_records=max(sc.n, 1),
-                      capacity_pairs=max(200 * sc.n, 1))
+def _grads(sc, params, cam, ts, long_list, spoil, persistent=False):
+    rast = Rasterizer([cam], sc.n, sc.sh_degree, tile_size=ts, long_list=long_list, persistent=persistent,
+                      capacity_records=max(sc.n, 1), capacity_pairs=max(200 * sc.n, 1))
     out = rast.forward(params)
     rng = np.random.default_rng(9)
     dl = rng.uniform(-1.0, 1.0, (3, cam.height, cam.width)).astype(np.float32)
@@ -62,15 +62,16 @@ def _grads(sc, params, cam, ts, long_list, spoil):
 
 @pytest.mark.parametrize("w, h, n, spoil", [(133, 101, 0, False), (133, 101, 1, False), (133, 101, 65, False),
                                             (133, 101, 3000, False), (133, 101, 3000, True),
-                                            (1293, 1021, 120_000, False), (1293, 1021, 120_000, True)])
+                                            (1693, 1301, 160_000, False), (1693, 1301, 160_000, True)])
 def test_backward_walks_agree(w, h, n, spoil):
-    """A wave per 16 px tile (every list under 32 entries; at 1293 x 1021
-    nearly all lists, as none holds a 4096th of the pairs) and a wave per 8 x 8
-    block (long_list 0, and the other tile sizes) form the same terms per
-    pixel and add them in another order: up to 24 additions of 2^-24 each,
-    1.4e-6 of the absolute terms, seven times that for their cancellation.  A
-    pixel whose gradient is not finite reaches the Gaussians it composited and
-    no others, in every walk."""
+    """A wave per 16 px tile (at 1693 x 1301, of more than 6,144 tiles, nearly
+    all lists, as none holds a 4096th of the pairs; with long_list 5 those
+    under 5 entries) and a wave per 8 x 8 block (long_list 0, the smaller
+    image, and the other tile sizes) form the same terms per pixel and add them
+    in another order: up to 24 additions of 2^-24 each, 1.4e-6 of the absolute
+    terms, seven times that for their cancellation.  A pixel whose gradient is
+    not finite reaches the Gaussians it composited and no others, in every
+    walk."""
     f = 120.0 * w / 133
     cam = camera(f, w, h)
     sc = _stack(n, 11 + n, 2.0, w, h, f)
@@ -78,6 +79,8 @@ def test_backward_walks_agree(w, h, n, spoil):
         sc.log_scale[:] -= 1.2
     params = device_params(sc)
     ref = _grads(sc, params, cam, 16, 1024, spoil)
+    queued = _grads(sc, params, cam, 16, 1024, spoil, persistent=True)
+    assert all(np.array_equal(ref[k], queued[k], equal_nan=True) for k in ref)
     for ts, long_list in ((16, 0), (16, 5), (8, 1024), (32, 1024)):
         got = _grads(sc, params, cam, ts, long_list, spoil)
         for k, a in ref.items():
