@@ -415,12 +415,12 @@ __device__ __forceinline__ int find_image(const FreqImg *imgs, int n, int64_t id
 // Deterministic sum over a workgroup of NW waves: butterfly per wave, then
 // the waves in order; the result is valid in every thread.
 template <int NW>
-__device__ __forceinline__ float block_sum(float x, float *red) {
+__device__ __forceinline__ double block_sum(double x, double *red) {
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off);
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = x;
   __syncthreads();
-  float t = red[0];
+  double t = red[0];
 #pragma unroll
   for (int w = 1; w < NW; ++w) t += red[w];
   return t;
@@ -490,16 +490,17 @@ __global__ __launch_bounds__(kFreqColThreads) __attribute__((amdgpu_waves_per_eu
 }
 
 // X of each image: its columns' sums in column order (thread t takes the
-// columns t mod 256 in order, then the fixed block sum).
+// columns t mod 256 in order, then the fixed block sum), in double precision:
+// the sum's own rounding had been most of X's error.
 __global__ __launch_bounds__(256) void k_freq_final(const FreqImg *__restrict__ imgs,
                                                     const float *__restrict__ col_sum, float *__restrict__ X) {
-  __shared__ float red[4];
+  __shared__ double red[4];
   const FreqImg im = imgs[blockIdx.x];
   const int half = im.w / 2 + 1;
-  float s = 0.0f;
+  double s = 0.0;
   for (int j = threadIdx.x; j < half; j += blockDim.x) s += col_sum[im.col_base + j];
-  const float total = block_sum<4>(s, red);
-  if (threadIdx.x == 0) X[blockIdx.x] = total;
+  const double total = block_sum<4>(s, red);
+  if (threadIdx.x == 0) X[blockIdx.x] = (float)total;
 }
 
 // Box average over n x n blocks; one thread per output value, the block's
