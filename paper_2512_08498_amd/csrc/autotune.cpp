@@ -214,10 +214,14 @@ extern "C" gsr_status gsr_autotune(gsr_ctx *c, const gsr_gaussians *g, const gsr
       known_rec = rec;
       if (cand.tile_size == 16) known_pairs16 = pairs;
     }
-    // warm-up, then the timed passes
+    // warm-up, then the timed passes; the first candidate, which the others
+    // have to beat, is timed again after as many passes: the chip that just
+    // left idle runs it up to 2% slower than the next
     if ((st = gsr_render_backward(c, g, cams_dev, n_views, ws.p, ws_bytes, &fo, dl.as<float>(), &gr, 0, s)) != GSR_OK)
       break;
-    for (int r = 0; r < repeats && st == GSR_OK; ++r) {
+    const int passes = (&cand == &candidates.front() ? 3 : 1) * repeats;
+    for (int i = 0; i < passes && st == GSR_OK; ++i) {
+      const int r = i % repeats;  // the last `repeats` passes count
       TUNE_HIP(hipEventRecord(ev.a, s));
       if ((st = gsr_render_forward(c, g, cams_dev, n_views, ws.p, ws_bytes, &fo, s)) != GSR_OK) break;
       if ((st = gsr_render_backward(c, g, cams_dev, n_views, ws.p, ws_bytes, &fo, dl.as<float>(), &gr, 0, s)) !=
