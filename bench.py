@@ -96,7 +96,7 @@ def stage_work(stage, n, n_u, pg, views, px, rec, pairs, tiles, evals):
 
 
 STEP_STAGES = ("preprocess", "binning", "sort", "raster_fwd", "loss", "raster_bwd", "reduce", "pre_bwd")
-STAGE_KERNEL = {"raster_bwd": "k_raster_bwd16", "raster_fwd": "k_raster_fwd16", "preprocess": "k_pre_write<3>",
+STAGE_KERNEL = {"raster_bwd": "k_raster_bwd16", "raster_fwd": "k_raster_fwd", "preprocess": "k_pre_write<3>",
                 "pre_bwd": "k_pre_bwd<3,true>"}
 
 
