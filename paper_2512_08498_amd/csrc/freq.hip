@@ -504,19 +504,24 @@ __global__ __launch_bounds__(256) void k_freq_final(const FreqImg *__restrict__ 
 }
 
 // Box average over n x n blocks; one thread per output value, the block's
-// values added row by row.
-__global__ __launch_bounds__(256) void k_downsample(const float *__restrict__ src, int W, int H, int n,
+// values added row by row.  I: 32-bit indices where they suffice (64-bit
+// divisions cost more than the reads).  N: n where it is known, so that its
+// reads are issued together.
+template <typename I, int N>
+__global__ __launch_bounds__(256) void k_downsample(const float *__restrict__ src, int W, int H, int n_,
                                                     float *__restrict__ dst) {
-  const int w = W / n, h = H / n;
-  const int64_t total = 3ll * w * h;
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int n = N ? N : n_;
+  const I w = (I)(W / n), h = (I)(H / n);
+  const I total = 3 * w * h;
+  const I idx = (I)blockIdx.x * (I)blockDim.x + (I)threadIdx.x;
   if (idx >= total) return;
-  const int x = (int)(idx % w);
-  const int y = (int)((idx / w) % h);
-  const int c = (int)(idx / ((int64_t)w * h));
+  const I row = idx / w, x = idx - row * w;
+  const I c = row / h, y = row - c * h;
   const float *p = src + ((int64_t)c * H + (int64_t)y * n) * W + (int64_t)x * n;
   float s = 0.0f;
+#pragma unroll
   for (int dy = 0; dy < n; ++dy)
+#pragma unroll
     for (int dx = 0; dx < n; ++dx) s += p[(int64_t)dy * W + dx];
   dst[idx] = s / (float)(n * n);
 }
@@ -587,7 +592,13 @@ void launch_freq_significance(const float *images, const FreqImg *imgs, int n_im
 void launch_downsample(const float *src, int W, int H, int n, float *dst, hipStream_t st) {
   const int64_t total = 3ll * (W / n) * (H / n);
   if (total == 0) return;
-  k_downsample<<<(unsigned)((total + 255) / 256), 256, 0, st>>>(src, W, H, n, dst);
+  const unsigned blocks = (unsigned)((total + 255) / 256);
+  if (total >= (int64_t(1) << 31))
+    k_downsample<int64_t, 0><<<blocks, 256, 0, st>>>(src, W, H, n, dst);
+  else if (n == 2)
+    k_downsample<uint32_t, 2><<<blocks, 256, 0, st>>>(src, W, H, n, dst);
+  else
+    k_downsample<uint32_t, 0><<<blocks, 256, 0, st>>>(src, W, H, n, dst);
 }
 
 void launch_freq_schedule(const float *x_gt, const float *x_gt_level, const float *x_render, int F, float tau_f,
