@@ -668,16 +668,20 @@ static gsr_status read_scalars(gsr_ctx *c, void *ws_base, void *stream, uint32_t
   }
   hipStream_t st = static_cast<hipStream_t>(stream);
   const char *src = static_cast<char *>(ws_base) + c->lay.scalars;
-  std::lock_guard<std::mutex> lock(c->host_lock);
-  if (!c->host_scalars) {  // the context's first reading; 64 bytes, 70 us
+  // the buffer is for one reader at a time; another, who must not wait for
+  // the first one's stream, copies to its own memory after its own wait
+  std::unique_lock<std::mutex> lock(c->host_lock, std::try_to_lock);
+  if (lock.owns_lock() && !c->host_scalars) {  // the context's first reading; 64 bytes, 70 us
     void *p = nullptr;
-    if (hipHostMalloc(&p, kNumScalars * 4) != hipSuccess) {
+    if (hipHostMalloc(&p, kNumScalars * 4) == hipSuccess)
+      c->host_scalars = static_cast<uint32_t *>(p);
+    else
       (void)hipGetLastError();
-      GSR_HIP(c, hipStreamSynchronize(st));
-      GSR_HIP(c, hipMemcpy(out, src, kNumScalars * 4, hipMemcpyDeviceToHost));
-      return GSR_OK;
-    }
-    c->host_scalars = static_cast<uint32_t *>(p);
+  }
+  if (!lock.owns_lock() || !c->host_scalars) {
+    GSR_HIP(c, hipStreamSynchronize(st));
+    GSR_HIP(c, hipMemcpy(out, src, kNumScalars * 4, hipMemcpyDeviceToHost));
+    return GSR_OK;
   }
   // copied in stream order, so the caller waits once: the host's part of a
   // checked forward and its backward 326 to 297 us
