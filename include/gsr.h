@@ -294,11 +294,13 @@ gsr_status gsr_profile_read(gsr_ctx *ctx, double *ms, int64_t *calls, int32_t re
  *  long_list  16 px tiles: in the backward, tiles with a long list are walked
  *             by a workgroup of four waves (an 8 x 8 quadrant each, one pixel
  *             per lane); the others take one wave each (four pixels per lane),
- *             four tiles per workgroup.  Below 32: lists of at least this many
- *             entries are long (0: every tile's).  From 32 on: those of at
- *             least a 4096th of the batch's pairs and 32 entries, which would
- *             outlast the rest of the launch.  In batches of at most 6,144
- *             tiles all are.
+ *             four tiles per workgroup.  Lists of at least this many entries
+ *             are long (to a 16th of an octave; 0: every tile's, 0xFFFFFFFF:
+ *             none), except that 1024, the default, leaves the choice to the
+ *             library: all lists in batches of at most 6,144 tiles, else those
+ *             of at least 32 entries and a 4096th of the batch's pairs, which
+ *             would outlast the rest of the launch.  The rounding of a view's
+ *             gradients may thus differ between batches of other views.
  *  persistent 0: one workgroup per work item (a tile, or at 16 px a group
  *             of four short tiles), dispatched by the hardware in the
  *             longest-first order.  1: a persistent launch of as many
@@ -488,8 +490,9 @@ gsr_status gsr_merge(gsr_ctx *ctx, const gsr_gaussians *g, int32_t view, const g
 /* Autotuner of the batched launch (the keyframe-window batches of Sec. 3.3
  * mix resolutions, so no one tile size suits all): times forward plus
  * backward on this batch for tile sizes 8, 16 and 32 and, at 16, for
- * long_list 1024 and 0, each with the grid and the persistent schedule
- * (gsr_tuning), and keeps the fastest (median of
+ * long_list in {1024, 512, 256, 0, 0xFFFFFFFF} (0 in batches of more than
+ * 6,144 tiles; up to there it is the launch of 1024), each with the grid and
+ * the persistent schedule (gsr_tuning), and keeps the fastest (median of
  * `repeats` >= 1 timed passes after one warm-up pass); candidates are tried
  * grid schedule first, 16 px with long_list 1024 first, and a later one is
  * kept only if at least 1% faster than the choice so far.

@@ -125,9 +125,14 @@ extern "C" gsr_status gsr_autotune(gsr_ctx *c, const gsr_gaussians *g, const gsr
     if (malformed) return ctx_error(c, GSR_ERR_INVALID_ARG, "malformed autotune cache line for this batch");
   }
 
+  // 0 is the launch of kLongAuto where that takes all lists as long
+  uint64_t tiles16 = 0;
+  for (int v = 0; v < n_views; ++v)
+    tiles16 += (uint64_t)std::max((cams_host[v].width + 15) / 16, 0) * (uint64_t)std::max((cams_host[v].height + 15) / 16, 0);
   std::vector<gsr_tuning> candidates;
   for (int pers = 0; pers < 2; ++pers) {
-    for (uint32_t ll : {1024u, 0u}) candidates.push_back({16, ll, pers, 0.f});
+    for (uint32_t ll : {kLongAuto, 512u, 256u, 0u, 0xFFFFFFFFu})
+      if (ll != 0u || tiles16 > kFewTiles) candidates.push_back({16, ll, pers, 0.f});
     candidates.push_back({8, 512u, pers, 0.f});
     candidates.push_back({32, 512u, pers, 0.f});
   }

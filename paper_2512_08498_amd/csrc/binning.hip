@@ -694,7 +694,8 @@ constexpr int kOrderNT = 1024;
 // 162, 176 and 181, four 800x450 views of 100k 107, 105, 105 and 106 (271
 // without).  A fixed length does not carry over: from 512 and 1024 entries
 // the whole rig takes 661 and 626 us (626 with the share), 40 mixed views 7.5
-// ms from 1024 (6.5).  long_list below kLongMin is taken as it is.
+// ms from 1024 (6.5).  This is the rule of kLongAuto; every other long_list is
+// the length that its caller wants.
 constexpr uint32_t kLongShare = 4096, kLongMin = 32;
 
 __device__ __forceinline__ uint32_t lower_bound(const uint32_t *__restrict__ a, uint32_t n, uint32_t x) {
@@ -737,7 +738,7 @@ __global__ __launch_bounds__(kOrderNT) void k_tile_ranges(Ws ws, Sizes sz, const
     codes[tile] = code;
     atomicAdd(&h[code], 1u);
   }
-  const uint32_t long_len = sz.long_list < kLongMin ? sz.long_list : max(kLongMin, ws.scalars[kNumPairs] / kLongShare);
+  const uint32_t long_len = sz.long_list == kLongAuto ? max(kLongMin, ws.scalars[kNumPairs] / kLongShare) : sz.long_list;
   (void)wave_atomic_inc(ws.scalars + kNumLong, valid && len >= long_len);
   __syncthreads();
   if (t < 256) code_hist[(size_t)blockIdx.x * 256 + t] = h[t];

@@ -72,7 +72,7 @@ struct Sizes {
   uint32_t cap_rec;
   uint32_t cap_pairs;
   uint32_t n_blocks;        // ceil(n / kPreBlock)
-  uint32_t long_list;       // gsr_tuning.long_list: which 16 px lists take a wave per 8 x 8 block (k_tile_ranges)
+  uint32_t long_list;       // gsr_tuning.long_list: 16 px lists this long take a wave per 8 x 8 block, or kLongAuto
   uint32_t persistent;      // compositing: 1 = persistent workgroups over a work queue (ItemQueue)
   uint32_t vis_words;       // ceil(n_views / 64)
   float bg[3];
@@ -82,6 +82,10 @@ constexpr int kPreBlock = 256;     // Gaussians per preprocess workgroup
 constexpr int kQueueLanes = 8;     // counters per work queue: one per XCD
 constexpr int kQueueStride = 32;   // words between counters (one 128-byte line each)
 constexpr int kLossBlocks = 2048;  // loss reduction partials
+constexpr uint32_t kLongAuto = 1024;  // long_list: the library chooses (k_tile_ranges, kFewTiles)
+// 16 px tiles up to which the library's choice of the long lists is all of
+// them, in k_raster_bwd (see there).
+constexpr uint32_t kFewTiles = 6144;
 
 // Image-model constants (float32 bit patterns written as hex literals).
 constexpr float kNearZ = 0x1.99999ap-3f;       // 0.2

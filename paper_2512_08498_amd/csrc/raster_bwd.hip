@@ -503,17 +503,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k
 }
 
 // A wave per 8 x 8 block for every tile, a tile per work item: 8 and 32 px,
-// and 16 px launches of at most kFewTiles tiles, which leave the chip room for
-// batches of 256 records (54 KB of LDS; all four waves stage, half the
-// barriers).  At 8 px four records at a time (921 us on the rig, two take 934;
-// one under branches took 1016); at 32 px, where 16 waves share a tile, two and
-// eight waves per SIMD (1331 us; four records and half the waves 1901; four
-// waves of four blocks each 1667).  At 16 px this walk and the mixed one above:
-// 64x48 with 2,000 Gaussians (12 tiles) 103 and 110 us, 1280x720 with 300k
-// (3,600) 178 and 191, 1600x900 with 300k (5,700) 147 and 158, 1920x1080 with
-// 500k (8,160) 228 and 200; 128- and 192-record batches take 108 and 107 us on
-// the first, eight records at a time 114.
-constexpr uint32_t kFewTiles = 6144;
+// and 16 px launches of at most kFewTiles tiles whose lists are all long (by
+// the library's choice, or long_list 0), which leave the chip room for batches
+// of 256 records (54 KB of LDS; all four waves stage, half the barriers).  At
+// 8 px four records at a time (921 us on the rig, two take 934; one under
+// branches took 1016); at 32 px, where 16 waves share a tile, two and eight
+// waves per SIMD (1331 us; four records and half the waves 1901; four waves of
+// four blocks each 1667).  At 16 px this walk and the mixed one above: 64x48
+// with 2,000 Gaussians (12 tiles) 103 and 110 us, 1280x720 with 300k (3,600)
+// 178 and 191, 1600x900 with 300k (5,700) 147 and 158, 1920x1080 with 500k
+// (8,160) 228 and 200; 128- and 192-record batches take 108 and 107 us on the
+// first, eight records at a time 114.
 
 template <int TS>
 struct BwdItem {
@@ -633,7 +633,7 @@ void launch_raster_bwd(const ViewInfo *views, const Ws &ws, const Sizes &sz, con
                        const uint32_t *last_pos, const float *dL_dimage, hipStream_t st) {
   if (sz.t_tot == 0) return;
 #define BWD_ARGS views, ws, sz, t_final, last_pos, dL_dimage
-  if (sz.ts == 16 && sz.t_tot <= kFewTiles) {
+  if (sz.ts == 16 && sz.t_tot <= kFewTiles && (sz.long_list == kLongAuto || sz.long_list == 0u)) {
     if (sz.persistent) launch_items<true>(k_raster_bwd<16, true>, sz.t_tot, BwdItem<16>::NT, st, BWD_ARGS);
     else launch_items<false>(k_raster_bwd<16, false>, sz.t_tot, BwdItem<16>::NT, st, BWD_ARGS);
     return;
