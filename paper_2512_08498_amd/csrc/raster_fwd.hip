@@ -42,8 +42,9 @@ struct FwdPixel {
   uint32_t last, cnt;
 };
 
-// G records from LDS.  Two ways to composite them, of the same results:
-// four at a time with selects only, so nothing stands between the alphas and
+// G records from LDS.  Two ways to composite them, of the same results where
+// the colours are finite (a weight of zero makes NaN of an infinite one, so
+// steps that hold one take the second way): four at a time with selects only, so nothing stands between the alphas and
 // T's chain (84 VGPRs, six waves per SIMD), for launches that cannot fill the
 // chip with waves, whose time is the longest lists' latency; or two at a time
 // with the lanes that do not composite switched off (five VALU instructions
@@ -151,6 +152,7 @@ __device__ __forceinline__ void fwd_block(const ViewInfo *__restrict__ views, co
     const bool keep = b0 + (uint32_t)lane < n && tile_reaches(p0, p1, p2, (float)ox, (float)oy, 8.0f);
     const uint64_t mask = __ballot(keep);
     const int kept = __popcll(mask);
+    const bool odd = G > 2 && __ballot(keep && !(fabsf(p2.z) + fabsf(p2.w) + fabsf(p3) < INFINITY)) != 0;
     __builtin_amdgcn_wave_barrier();
     if (keep) {
       float4 *dst = L.rec[__popcll(mask & lanemask_lt())];
@@ -167,6 +169,10 @@ __device__ __forceinline__ void fwd_block(const ViewInfo *__restrict__ views, co
     if (b0 + kWave < n) {
       payload(rec);
       rec_n = ids(b0 + 2 * kWave);
+    }
+    if (G > 2 && odd) {
+      for (int k = 0; k < kept; k += 2) fwd_group<2>(L.rec + k, s);
+      continue;
     }
     for (int k = 0; k < kept; k += G) {
       fwd_group<G>(L.rec + k, s);
