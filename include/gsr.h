@@ -369,7 +369,9 @@ gsr_status gsr_freq_plan(gsr_ctx *ctx, const int32_t *widths, const int32_t *hei
 /* X of every planned image: images holds them planar [3][h][w], one after
  * the other in plan order (the layout of gsr_fwd_out.image); X [n_images].
  * workspace: DEVICE, 256-byte aligned, of the planned size (the half spectra
- * of the batch, 24 bytes per pixel and column pair).  Deterministic.      */
+ * of the batch, 24 bytes per bin of the w / 2 + 1 columns of h bins, odd h
+ * rounded up).  Deterministic, and the same bits whatever an image is planned
+ * with.                                                                    */
 gsr_status gsr_freq_significance(gsr_ctx *ctx, const float *images, void *workspace, size_t workspace_bytes,
                                  float *X, void *stream);
 

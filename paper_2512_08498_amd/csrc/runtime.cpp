@@ -232,7 +232,9 @@ float *cam_part(const gsr_ctx *c, void *base) { return reinterpret_cast<float *>
 // radix writes to few LDS banks, so an odd one goes first where there is one.
 // Radices below 5 (many butterflies, held over a barrier in a middle stage)
 // are first, or last in the column pass (cols), whose last stage is another
-// than its first and takes the three channels in turn.
+// than its first and takes the three channels in turn.  cnt is that of a full
+// workgroup, which depends on the image's size alone: the rounding of X follows
+// the radices, and X of an image is the same bits whatever it is planned with.
 bool fft_plan(int n, int cnt, bool cols, uint8_t *fac, int32_t &nfac) {
   struct Radix {
     int p, ops;
@@ -283,11 +285,15 @@ bool fft_plan(int n, int cnt, bool cols, uint8_t *fac, int32_t &nfac) {
   return true;
 }
 
-// Pairs of rows, or columns, per workgroup: what fits into `elems` values,
-// while that leaves `groups` workgroups of the batch's `total`.
-int freq_group(int n, int elems, int64_t total, int groups, int most) {
-  const int64_t k = std::min<int64_t>(elems / (3 * n), total / groups);
-  return (int)std::max<int64_t>(1, std::min<int64_t>(most, k));
+// Pairs of rows, or columns, of a full workgroup: what fits into `elems`
+// values, at most the image's own.  A batch takes fewer per workgroup while
+// that leaves it fewer than kFreqRowGroups, or kFreqColGroups, of them.
+int freq_group(int n, int elems, int most) { return std::max(1, std::min(most, elems / (3 * n))); }
+
+// Row pairs are taken in powers of two: whole 32, 64, ... bytes of a column.
+int pow2_floor(int64_t k) {
+  while (k & (k - 1)) k &= k - 1;
+  return (int)k;
 }
 
 // The twiddles of a transform's stages after the first.
@@ -793,10 +799,11 @@ gsr_status gsr_freq_plan(gsr_ctx *c, const int32_t *widths, const int32_t *heigh
     f.h = heights[i];
     if (f.w < 1 || f.h < 1 || f.w > kFreqMaxN || f.h > kFreqMaxN)
       return fail(c, GSR_ERR_UNSUPPORTED, "image %d: %d x %d outside 1..%d", i, f.w, f.h, kFreqMaxN);
-    f.pairs = freq_group(f.w, kFreqRowElems, all_pairs, kFreqRowGroups, (f.h + 1) / 2);
-    while (f.pairs & (f.pairs - 1)) f.pairs &= f.pairs - 1;  // whole 32, 64, ... bytes of a column
-    f.cols = freq_group(f.h, kFreqColElems, all_cols, kFreqColGroups, f.w / 2 + 1);
-    if (!fft_plan(f.w, 3 * f.pairs, false, f.fac_w, f.nfac_w) || !fft_plan(f.h, 3 * f.cols, true, f.fac_h, f.nfac_h))
+    const int pairs = freq_group(f.w, kFreqRowElems, (f.h + 1) / 2), cols_each = freq_group(f.h, kFreqColElems, f.w / 2 + 1);
+    f.pairs = pow2_floor(std::min<int64_t>(pairs, std::max<int64_t>(1, all_pairs / kFreqRowGroups)));
+    f.cols = (int)std::min<int64_t>(cols_each, std::max<int64_t>(1, all_cols / kFreqColGroups));
+    if (!fft_plan(f.w, 3 * pow2_floor(pairs), false, f.fac_w, f.nfac_w) ||
+        !fft_plan(f.h, 3 * cols_each, true, f.fac_h, f.nfac_h))
       return fail(c, GSR_ERR_UNSUPPORTED, "image %d: %d x %d has a prime factor above 7", i, f.w, f.h);
     const int64_t half = f.w / 2 + 1;
     f.pix_off = pix;
