@@ -23,6 +23,9 @@
 // conservative, so the composited sequence of every pixel is unchanged.
 #pragma once
 
+#include <algorithm>
+#include <atomic>
+
 #include "common.hpp"
 #include "util.hpp"
 
@@ -115,18 +118,33 @@ struct ItemQueue {
   }
 };
 
-// Workgroups of a persistent launch: compute units times the workgroups of
-// `kernel` (of `threads` threads) that one holds at once, a multiple of the
-// queue's lanes.
-template <typename K>
-inline uint32_t persistent_grid(K kernel, int threads) {
+// Workgroups of a persistent launch: the current device's compute units times
+// the workgroups of Kernel (of `threads` threads) that one holds at once, a
+// multiple of the queue's lanes.  Asked of the runtime once per kernel and
+// device; the kernel is a template argument, as kernels of one signature hold
+// from two to twenty workgroups per compute unit.
+template <auto Kernel>
+inline uint32_t persistent_grid(int threads) {
+  constexpr int kDevices = 64;
+  static std::atomic<uint32_t> known[kDevices];
   int dev = 0, cus = 0, per = 0;
-  if (hipGetDevice(&dev) != hipSuccess ||
-      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
+  const bool have_dev = hipGetDevice(&dev) == hipSuccess;
+  const bool cached = have_dev && dev >= 0 && dev < kDevices;
+  if (cached)
+    if (const uint32_t g = known[dev].load(std::memory_order_relaxed)) return g;
+  if (!have_dev || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
     cus = 256;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, kernel, threads, 0) != hipSuccess || per < 1) per = 1;
-  const uint32_t g = (uint32_t)(cus * per) / kQueueLanes * kQueueLanes;
-  return g < (uint32_t)kQueueLanes ? (uint32_t)kQueueLanes : g;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, Kernel, threads, 0) != hipSuccess || per < 1) per = 1;
+  const uint32_t g = std::max((uint32_t)(cus * per) / kQueueLanes * kQueueLanes, (uint32_t)kQueueLanes);
+  if (cached) known[dev].store(g, std::memory_order_relaxed);
+  return g;
+}
+
+// Grid schedule (P = false): a workgroup per work item, `items` of them at
+// most.  Persistent: the device's resident workgroups.
+template <bool P, auto Kernel, class... A>
+inline void launch_items(uint32_t items, int threads, hipStream_t st, A... args) {
+  Kernel<<<P ? persistent_grid<Kernel>(threads) : items, threads, 0, st>>>(args...);
 }
 
 }  // namespace gsr

@@ -639,33 +639,22 @@ __global__ __launch_bounds__(256) void k_reduce_pairs(Ws ws, int32_t *step) {
   }
 }
 
-// Grid or persistent schedule, as the forward (launch_items there).
-template <bool P, class K, class... A>
-static void launch_items(K kernel, uint32_t t_tot, int threads, hipStream_t st, A... args) {
-  uint32_t grid = t_tot;
-  if (P) {
-    static const uint32_t pgrid = persistent_grid(kernel, threads);
-    grid = pgrid;
-  }
-  kernel<<<grid, threads, 0, st>>>(args...);
-}
-
 void launch_raster_bwd(const ViewInfo *views, const Ws &ws, const Sizes &sz, const float *t_final,
                        const uint32_t *last_pos, const float *dL_dimage, hipStream_t st) {
   if (sz.t_tot == 0) return;
 #define BWD_ARGS views, ws, sz, t_final, last_pos, dL_dimage
   if (sz.ts == 16 && sz.t_tot <= kFewTiles && (sz.long_list == kLongAuto || sz.long_list == 0u)) {
-    if (sz.persistent) launch_items<true>(k_raster_bwd<16, true>, sz.t_tot, BwdItem<16>::NT, st, BWD_ARGS);
-    else launch_items<false>(k_raster_bwd<16, false>, sz.t_tot, BwdItem<16>::NT, st, BWD_ARGS);
+    if (sz.persistent) launch_items<true, k_raster_bwd<16, true>>(sz.t_tot, BwdItem<16>::NT, st, BWD_ARGS);
+    else launch_items<false, k_raster_bwd<16, false>>(sz.t_tot, BwdItem<16>::NT, st, BWD_ARGS);
     return;
   }
   switch ((sz.ts << 1) | (sz.persistent ? 1 : 0)) {
-    case 16: launch_items<false>(k_raster_bwd<8, false>, sz.t_tot, BwdItem<8>::NT, st, BWD_ARGS); break;
-    case 17: launch_items<true>(k_raster_bwd<8, true>, sz.t_tot, BwdItem<8>::NT, st, BWD_ARGS); break;
-    case 64: launch_items<false>(k_raster_bwd<32, false>, sz.t_tot, BwdItem<32>::NT, st, BWD_ARGS); break;
-    case 65: launch_items<true>(k_raster_bwd<32, true>, sz.t_tot, BwdItem<32>::NT, st, BWD_ARGS); break;
-    case 33: launch_items<true>(k_raster_bwd16<true>, sz.t_tot, 256, st, BWD_ARGS); break;
-    default: launch_items<false>(k_raster_bwd16<false>, sz.t_tot, 256, st, BWD_ARGS); break;
+    case 16: launch_items<false, k_raster_bwd<8, false>>(sz.t_tot, BwdItem<8>::NT, st, BWD_ARGS); break;
+    case 17: launch_items<true, k_raster_bwd<8, true>>(sz.t_tot, BwdItem<8>::NT, st, BWD_ARGS); break;
+    case 64: launch_items<false, k_raster_bwd<32, false>>(sz.t_tot, BwdItem<32>::NT, st, BWD_ARGS); break;
+    case 65: launch_items<true, k_raster_bwd<32, true>>(sz.t_tot, BwdItem<32>::NT, st, BWD_ARGS); break;
+    case 33: launch_items<true, k_raster_bwd16<true>>(sz.t_tot, 256, st, BWD_ARGS); break;
+    default: launch_items<false, k_raster_bwd16<false>>(sz.t_tot, 256, st, BWD_ARGS); break;
   }
 #undef BWD_ARGS
 }

@@ -265,18 +265,6 @@ __global__ __launch_bounds__(FwdItem<TS>::NW * 64) void k_raster_fwd(
 // Work items, and loss partials, of the forward.
 uint32_t raster_fwd_grid(const Sizes &sz) { return sz.ts == 8 ? (sz.t_tot + 3u) / 4u : sz.t_tot; }
 
-// Grid schedule: one workgroup per item.  Persistent: the device's resident
-// workgroups.
-template <bool P, class K, class... A>
-static void launch_items(K kernel, uint32_t items, int threads, hipStream_t st, A... args) {
-  uint32_t grid = items;
-  if (P) {
-    static const uint32_t pgrid = persistent_grid(kernel, threads);
-    grid = pgrid;
-  }
-  kernel<<<grid, threads, 0, st>>>(args...);
-}
-
 // Waves up to which a launch takes the group of four records: at 22,800 waves
 // of long street lists four take 143 us and two 176, at 34,800 294 and 363,
 // at 45,600 197 and 185 and at 136,800 400 and 347.
@@ -287,8 +275,8 @@ void launch_raster_fwd(const ViewInfo *views, const Ws &ws, const Sizes &sz, flo
   if (sz.t_tot == 0) return;
   const bool few = (uint64_t)sz.t_tot * (uint64_t)(sz.ts * sz.ts / 64) <= kFwdFewWaves;
 #define FWD(TS, P, G)                                                                                             \
-  launch_items<P>(k_raster_fwd<TS, P, G>, raster_fwd_grid(sz), FwdItem<TS>::NW * 64, st, views, ws, sz, image,    \
-                  t_final, last_pos, n_contrib, la)
+  launch_items<P, k_raster_fwd<TS, P, G>>(raster_fwd_grid(sz), FwdItem<TS>::NW * 64, st, views, ws, sz, image,    \
+                                          t_final, last_pos, n_contrib, la)
 #define FWD_TS(TS)                                    \
   if (sz.persistent) {                                \
     if (few) FWD(TS, true, 4); else FWD(TS, true, 2); \
