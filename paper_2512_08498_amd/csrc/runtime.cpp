@@ -675,7 +675,8 @@ static gsr_status read_scalars(gsr_ctx *c, void *ws_base, void *stream, uint32_t
   hipStream_t st = static_cast<hipStream_t>(stream);
   const char *src = static_cast<char *>(ws_base) + c->lay.scalars;
   // the buffer is for one reader at a time; another, who must not wait for
-  // the first one's stream, copies to its own memory after its own wait
+  // the first one's stream, copies to its own (pageable) memory in the order
+  // of its own: the null stream's copy would wait for streams that block
   std::unique_lock<std::mutex> lock(c->host_lock, std::try_to_lock);
   if (lock.owns_lock() && !c->host_scalars) {  // the context's first reading; 64 bytes, 70 us
     void *p = nullptr;
@@ -685,8 +686,8 @@ static gsr_status read_scalars(gsr_ctx *c, void *ws_base, void *stream, uint32_t
       (void)hipGetLastError();
   }
   if (!lock.owns_lock() || !c->host_scalars) {
+    GSR_HIP(c, hipMemcpyAsync(out, src, kNumScalars * 4, hipMemcpyDeviceToHost, st));
     GSR_HIP(c, hipStreamSynchronize(st));
-    GSR_HIP(c, hipMemcpy(out, src, kNumScalars * 4, hipMemcpyDeviceToHost));
     return GSR_OK;
   }
   // copied in stream order, so the caller waits once: the host's part of a

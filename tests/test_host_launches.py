@@ -1,10 +1,12 @@
 """The library's host code on fake HIP calls (fake_hip.cpp, in a process of its
-own; no GPU): the launch grids of the persistent schedule."""
+own; no GPU): the launch grids of the persistent schedule, and readers of the
+counters on streams of their own."""
 import ctypes as C
 import importlib.util
 import os
 import subprocess
 import sys
+import threading
 
 import pytest
 
@@ -33,6 +35,14 @@ def test_persistent_grids_fit_their_kernels(fake):
     """A persistent launch has the workgroups that its own kernel keeps on the
     device, whichever kernels were launched before, on each device."""
     _run(fake, "grids")
+
+
+def test_a_second_reader_of_the_counters_keeps_to_its_stream(fake):
+    """gsr_check in two threads on two streams, the first one's not done: the
+    second returns at once, with the counters of its own workspace, and copies
+    on its own stream only (the null stream waits for the first one's where
+    that blocks, and later work on it for this copy)."""
+    _run(fake, "readers")
 
 
 # ---- in the process with the fake calls
@@ -90,5 +100,35 @@ def _grids(fake):
     assert len(seen) == 6 + 4, seen  # the forwards' two groups, the backwards of 16 px few and many
 
 
+def _readers(fake):
+    f, L, lib = _load(fake)
+    ctx, cams, ws, size, raw = _plan(L, lib, 16, 64, 48)
+    second = (C.c_char * (size + 256))()
+    ws2 = (C.addressof(second) + 255) // 256 * 256
+    (C.c_uint32 * 3).from_address(ws)[:] = [3, 5, 0]
+    (C.c_uint32 * 3).from_address(ws2)[:] = [7, 9, 0]
+
+    def read(w, stream, into):
+        c = [C.c_int64() for _ in range(3)]
+        assert lib.gsr_required_capacity(ctx, C.c_void_p(w), *[C.byref(x) for x in c], C.c_void_p(stream)) == 0
+        into[:] = [c[0].value, c[1].value]
+
+    a, b, alone = [], [], []
+    read(ws, 16, alone)
+    f.fake_hold(32)
+    t = threading.Thread(target=read, args=(ws, 32, a))
+    t.start()
+    assert f.fake_wait_until_held()
+    f.fake_clear()
+    read(ws2, 48, b)
+    copies = f.fake_text().decode().splitlines()
+    assert not a, "the first reader's stream was not done"
+    f.fake_release()
+    t.join()
+    print(alone, a, b, copies)
+    assert (alone, a, b) == ([3, 5], [3, 5], [7, 9])
+    assert copies == ["copy on stream 48"]
+
+
 if __name__ == "__main__":
-    {"grids": _grids}[sys.argv[2]](sys.argv[1])
+    {"grids": _grids, "readers": _readers}[sys.argv[2]](sys.argv[1])
