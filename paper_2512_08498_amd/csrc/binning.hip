@@ -83,7 +83,10 @@ __global__ __launch_bounds__(256) void k_emit(Ws ws, Sizes sz,
       tbase = rc.z - ty0 * rc.w - tx0;  // so that tbase + ty * pitch + tx is the tile's id
       tpitch = rc.w;
       off = offs[i];
-      if (off + cnt > sz.cap_pairs) {  // inconsistent pair offsets
+      const uint32_t last = rc.z + ((rc.y >> 16) - ty0) * rc.w + (tx1 - tx0);
+      // inconsistent pair offsets, or a tile that the plan has not (the sort
+      // takes the bits that the tiles need, so nothing behind it would see one)
+      if (off + cnt > sz.cap_pairs || max(rc.z, last) >= sz.t_tot) {
         ws.scalars[kOverflow] = 3u;
         cnt = 0;
       }
