@@ -67,9 +67,6 @@ struct GroupN {
   static constexpr int N = NN;
 };
 
-// Three waves per SIMD: the CAM variant's extra live values would otherwise
-// push the degree-3 kernel past 168 registers and down to one or two waves,
-// which costs more than the few spills that keep it at three.
 // What passes the caches by, from this many parameter values of the state on:
 // the moments, which nothing else reads, and the parameters, which the next
 // forward reads first.  A training step of two 960x540 views (before, moments
@@ -90,6 +87,9 @@ __device__ __forceinline__ void store_past(float *p, float x) {
 
 // ADAM: 0 gradients only, 1 with the update, 2 the moments and 3 the
 // parameters too past the caches.
+// Three waves per SIMD: the CAM variant's extra live values would otherwise
+// push the degree-3 kernel past 168 registers and down to one or two waves,
+// which costs more than the few spills that keep it at three.
 template <int DEG, int ADAM, bool CAM>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_pre_bwd(
     GaussPtrs gp, const Cam *__restrict__ cams, Ws ws, Sizes sz, MutPtrs grads, int accumulate, AdamArgs adam,

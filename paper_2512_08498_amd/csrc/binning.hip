@@ -353,7 +353,7 @@ __global__ __launch_bounds__(kScanNT) void k_scan_down(uint32_t *__restrict__ da
 
 // 2c. Stable scatter of one block's chunk by digit, from the row prefixes and
 // totals of its digits.  Wave w owns the w-th
-// quarter of the chunk and loads all of it first (IPL items per lane).  It
+// eighth of the chunk and loads all of it first (IPL items per lane).  It
 // ranks its items by digit round by round (64 items, in order) with ballot
 // matches and its own running digit counts in LDS, so no workgroup barrier
 // is needed per round.  The block then places its items in LDS in local
@@ -499,9 +499,15 @@ __global__ __launch_bounds__(kRdxNT) void k_digit_scatter(const uint32_t *__rest
 // Small inputs (at most kMergeMax items, on the host's capacity) are sorted
 // in two launches instead of three per digit: each workgroup sorts a run of
 // kRunItems items in LDS (all digits), then every item finds its place by
-// searching the other runs.  At 25k live records the depth sort's four passes
-// take 63 us, these two kernels 20; the searches grow with the square of the
-// item count, so larger inputs take the passes.
+// searching the other runs.  The searches grow with the square of the item
+// count, so larger inputs take the passes.  A whole forward with either, the
+// live items being less than the capacity of 65,536 (1920x1080): the depth sort
+// (four passes) of 4,000 records 100 us and 123, of 25,000 110 and 133, of
+// 65,000 124 and 139; the tile sort where it would take two passes (8,160 tiles)
+// of 4,600 pairs 94 and 98, of 33,000 113 and 109, of 64,000 126 and 121, and
+// where it would take one (1,450 tiles) 80 and 79, 90 and 88, 110 and 99.  So
+// the line is the depth sort's; the tile sort, which would rather end at 30,000
+// pairs or none, loses less there than the depth sort gains.
 constexpr int kRunNT = 1024, kRunIPL = 4;
 constexpr uint32_t kRunItems = kRunNT * kRunIPL;
 constexpr uint32_t kMergeMax = 16 * kRunItems;

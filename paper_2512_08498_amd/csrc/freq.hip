@@ -21,7 +21,7 @@
 // radix over all sequences of the workgroup at once, in one LDS buffer: the
 // first stage's butterflies are loaded from global memory, and the column
 // pass's last stage keeps its bins in registers.  The twiddles come from a
-// table per transform length computed in double precision at plan time, in
+// table per list of radices computed in double precision at plan time, in
 // the order in which the stages read them.
 //
 // What bounds the two passes is the LDS and the stages' latency, not HBM (the
@@ -167,8 +167,8 @@ __device__ __forceinline__ void dft_composite(float2 *v) {
     for (int b = 0; b < B; ++b) v[a + A * b] = t[a * B + b];
 }
 
-// In-register radix-P DFT with the forward sign (P = 1: nothing).  Radices 3 and 5 use the
-// symmetric forms: with s_k = x_k + x_{P-k} and d_k = x_k - x_{P-k},
+// In-register radix-P DFT with the forward sign (P = 1: nothing).  Radices 3
+// and 5 use the symmetric forms: with s_k = x_k + x_{P-k} and d_k = x_k - x_{P-k},
 // X_q = x_0 + sum_k cos(2 pi k q / P) s_k - i sum_k sin(2 pi k q / P) d_k.
 template <int P>
 __device__ __forceinline__ void dft(float2 *v) {
@@ -226,8 +226,8 @@ __device__ __forceinline__ void dft(float2 *v) {
 }
 
 
-// The workgroup's buffer: an LDS pointer of its own kind, so that the stages,
-// which are calls, take ds_ instructions.
+// The workgroup's buffer: an LDS pointer of its own kind, so that the stages
+// take ds_ instructions.
 typedef float v2f __attribute__((ext_vector_type(2)));
 typedef __attribute__((address_space(3))) v2f Lds2;
 
@@ -246,8 +246,8 @@ __device__ __forceinline__ void put(Lds2 *p, float2 x) {
 // the other.  Butterfly b (sequence b / m, index j = b mod m, m = N / P)
 // reads elements j + r m, multiplies by the twiddles exp(-2 pi i k r / (Ns P))
 // (k = j mod Ns; table entry (r - 1) Ns + k of the stage), transforms, and
-// writes (j / Ns) Ns P + k + q Ns.  The stages are not inlined: each radix
-// then gets its own register allocation.
+// writes (j / Ns) Ns P + k + q Ns.  The stages are inlined: as calls they saved
+// registers to scratch.
 
 // First stage (Ns = 1, no twiddles) of the row pass: sequence 3 p + c packs
 // rows row0 + 2 p and the next of channel c (zeros past the last row).

@@ -491,13 +491,16 @@ union BwdLds16 {
   BwdWaveLds wave[4];
 };
 
-// VALU issue bounds it (447M instructions a launch on the rig, 529M when every
+// VALU issue bounds it (416M instructions a launch on the rig, 529M when every
 // lane kept three suffix colours, composited under selects and the wave sums
-// took 33 instructions): six 1600x900 views of 1M Gaussians 645 us (785), 40
-// mixed views of 2M 6.5 ms (7.8).  Five waves per SIMD: four (110 VGPRs) took
-// 768 us, six (with 64-record batches) 672 but 6.8 ms on the 40 views.  The
-// blocks' masks by tile_reaches, as in the forward, instead of by the boxes
-// took 703 us and 6.9 ms.
+// took 33 instructions): six 1600x900 views of 1M Gaussians 643 us (785).  Five
+// waves per SIMD and the blocks' masks from the boxes, from one build (rig; 40
+// mixed views of 2M, two scenes; six 800x450 views of 300k, one long list):
+//   as it is                            643 us  7.71 ms  6.43 ms  318 us
+//   four waves                          642     7.67     6.57     318
+//   six waves, 64-record batches        636     7.56     6.47     353
+//   masks by tile_reaches per block     648     7.54     6.63     316
+//   the same behind the tile's test     653     7.75     6.69     322
 template <bool P>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k_raster_bwd16(
     const ViewInfo *__restrict__ views, Ws ws, Sizes sz, const float *__restrict__ t_final,

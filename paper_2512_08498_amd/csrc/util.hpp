@@ -71,9 +71,7 @@ __device__ __forceinline__ T wave_reduce_max(T x) {
   return x;
 }
 
-// Sum over the wave with DPP row operations; the total is valid in lane 63.
-// Must be called with all 64 lanes active.
-// Swap-and-add of two row-summed values a, b: lanes 0..31 get
+// Swap-and-add of two values a, b over the wave's halves: lanes 0..31 get
 // a[l] + a[l + 32], lanes 32..63 get b[l - 32] + b[l].
 __device__ __forceinline__ float fold32(float a, float b) {
   const auto h = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
@@ -81,8 +79,8 @@ __device__ __forceinline__ float fold32(float a, float b) {
 }
 
 // Swap-and-add of two fold32 results x (values A | B) and y (C | D): lanes
-// 0..15 get A, 16..31 get C, 32..47 get B, 48..63 get D, each summed over
-// the whole wave.
+// 0..15 get A, 16..31 get C, 32..47 get B, 48..63 get D, each added up over
+// the rows of 16 lanes.
 __device__ __forceinline__ float fold16(float x, float y) {
   const auto h = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(y), false, false);
   return __uint_as_float(h[0]) + __uint_as_float(h[1]);
@@ -107,8 +105,8 @@ __device__ __forceinline__ float pack_add(float a, float b, bool hi) {
 // (9 -> 5 -> 3), rotate 8 and the half-row mirror keep one value of a pair per
 // lane (3 -> 2 -> 1), and the quad permutes complete the sums: 25
 // instructions (33 when the pairwise steps came first, at two selects a pair).
-// On return the sum of v[k] is in lane sum9_lane(k) (and the rest of its
-// quad).  Fixed order (deterministic); every lane must be active.
+// On return sum9_value says whose sum a lane holds.  Fixed order
+// (deterministic); every lane must be active.
 __device__ __forceinline__ float wave_sum9_packed(const float (&v)[9]) {
   const int l = lane_id();
   const bool b2 = (l >> 2) & 1, b3 = (l >> 3) & 1;
@@ -123,16 +121,12 @@ __device__ __forceinline__ float wave_sum9_packed(const float (&v)[9]) {
   return dpp_add<kXor2>(s, s);
 }
 
-// First lane holding the sum of v[k] after wave_sum9_packed, and its inverse:
-// the value whose sum this lane is to write, or -1.
-__device__ __forceinline__ constexpr int sum9_lane(int k) {
-  return k == 8 ? 4 : ((k & 1) << 5) | ((k & 2) << 3) | ((k & 4) << 1);
-}
+// The value whose sum this lane is to write after wave_sum9_packed, or -1: each
+// is in the four lanes of a quad, of which the first writes it.
 __device__ __forceinline__ int sum9_value(int lane) {
   if (lane == 4) return 8;
   return (lane & 7) ? -1 : (lane >> 5) | ((lane >> 3) & 2) | ((lane >> 1) & 4);
 }
-
 
 // Lanes below this one in the wave.
 __device__ __forceinline__ uint64_t lanemask_lt() { return (uint64_t(1) << lane_id()) - 1u; }
