@@ -127,8 +127,10 @@ extern "C" gsr_status gsr_autotune(gsr_ctx *c, const gsr_gaussians *g, const gsr
 
   // 0 is the launch of kLongAuto where that takes all lists as long
   uint64_t tiles16 = 0;
-  for (int v = 0; v < n_views; ++v)
-    tiles16 += (uint64_t)std::max((cams_host[v].width + 15) / 16, 0) * (uint64_t)std::max((cams_host[v].height + 15) / 16, 0);
+  for (int v = 0; v < n_views; ++v) {
+    const int64_t w = std::max(cams_host[v].width, 0), h = std::max(cams_host[v].height, 0);
+    tiles16 += (uint64_t)((w + 15) / 16 * ((h + 15) / 16));
+  }
   std::vector<gsr_tuning> candidates;
   for (int pers = 0; pers < 2; ++pers) {
     for (uint32_t ll : {kLongAuto, 512u, 256u, 0u, 0xFFFFFFFFu})
